@@ -216,6 +216,10 @@ hipError_t launch_copy_variant(int v, const double* src, double* dst, long long 
 constexpr int kTriadVariants = 3;
 hipError_t launch_triad_variant(int v, const double* a, const double* b, double* dst, long long n,
                                 hipStream_t st);
+// The box of ex x ey x ez doubles at src (row and plane strides ssy, ssz) to
+// dst (dsy, dsz); the boxes may not overlap.
+hipError_t launch_copy_box(const double* src, long long ssy, long long ssz, double* dst, long long dsy,
+                           long long dsz, int ex, int ey, int ez, hipStream_t st);
 hipError_t launch_copy_interior(const double* src, double* dst, int nx, int ny, int nz,
                                 long long ssy, long long ssz, long long dsy, long long dsz,
                                 hipStream_t st);

@@ -280,13 +280,19 @@ __global__ void k_triad_tail(const double* __restrict__ a, const double* __restr
   if (threadIdx.x == 0 && (n & 1)) dst[n - 1] = a[n - 1] + b[n - 1];
 }
 
+// A box of ex x ey x ez doubles between two layouts: one wavefront per row
+// (x contiguous in both), rows taken in turn by the grid's wavefronts, so
+// that short rows cost one access each and not a workgroup.
 __global__ void __launch_bounds__(256)
-    k_copy_interior(const double* __restrict__ src, double* __restrict__ dst, int nx, long long ssy,
-                    long long ssz, long long dsy, long long dsz) {
-  const int i = 1 + blockIdx.x * 256 + threadIdx.x;
-  const int j = 1 + blockIdx.y;
-  const int k = 1 + blockIdx.z;
-  if (i <= nx) dst[i + dsy * j + dsz * k] = src[i + ssy * j + ssz * k];
+    k_copy_box(const double* __restrict__ src, long long ssy, long long ssz, double* __restrict__ dst,
+               long long dsy, long long dsz, int ex, int ey, int nrows) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  for (int row = blockIdx.x * 4 + (int)(threadIdx.x / WAVE); row < nrows; row += gridDim.x * 4) {
+    const int k = row / ey, j = row - k * ey;
+    const double* s = src + ssy * j + ssz * k;
+    double* d = dst + dsy * j + dsz * k;
+    for (int i = lane; i < ex; i += WAVE) d[i] = s[i];
+  }
 }
 
 __global__ void k_set_int(int* p, int n, int v) {
@@ -554,12 +560,20 @@ hipError_t launch_copy(const double* src, double* dst, long long n, hipStream_t 
   return hipGetLastError();
 }
 
+hipError_t launch_copy_box(const double* src, long long ssy, long long ssz, double* dst, long long dsy,
+                           long long dsz, int ex, int ey, int ez, hipStream_t st) {
+  const long long nrows = (long long)ey * ez;
+  if (ex <= 0 || nrows <= 0) return hipSuccess;
+  if (nrows >= (1LL << 31) - 4 * 8192) return hipErrorInvalidValue;
+  const int grid = static_cast<int>(min((nrows + 3) / 4, 8192LL));
+  hipLaunchKernelGGL(k_copy_box, dim3(grid), dim3(256), 0, st, src, ssy, ssz, dst, dsy, dsz, ex, ey, (int)nrows);
+  return hipGetLastError();
+}
+
 hipError_t launch_copy_interior(const double* src, double* dst, int nx, int ny, int nz,
                                 long long ssy, long long ssz, long long dsy, long long dsz,
                                 hipStream_t st) {
-  dim3 grid((nx + 255) / 256, ny, nz);
-  hipLaunchKernelGGL(k_copy_interior, grid, dim3(256), 0, st, src, dst, nx, ssy, ssz, dsy, dsz);
-  return hipGetLastError();
+  return launch_copy_box(src + (1 + ssy + ssz), ssy, ssz, dst + (1 + dsy + dsz), dsy, dsz, nx, ny, nz, st);
 }
 
 hipError_t launch_set_int(int* p, int n, int v, hipStream_t st) {

@@ -163,3 +163,34 @@ def test_fp64_serving_budget_uses_fp64_state():
     # one at a time
     for k in range(1, 3):
         assert order[k]["t_admit"] >= order[k - 1]["t_done"] - 1e-3
+
+
+@pytest.mark.parametrize("precision", [j3d.SERVE_MIXED, j3d.SERVE_FP64])
+def test_host_arrays_of_ragged_requests(precision):
+    """Right-hand sides from and solutions to packed host arrays: extents of
+    one, below, at and above a wavefront's width, a halo in f that must not
+    matter, u's halo zero and its whole array written; bits of the oracle."""
+    shapes = [(1, 1, 1), (5, 70, 3), (62, 4, 9), (64, 3, 5), (65, 33, 2), (130, 1, 4)]
+    say("serve host arrays", precision)
+    with j3d.Server(hbm_budget_bytes=1 << 30, max_slots=3, cycle_sweeps=10, precision=precision) as s:
+        tickets, us, fs = {}, [], []
+        for k, (nx, ny, nz) in enumerate(shapes):
+            f = synth.uniform_field(nx, ny, nz, 90 + k, synth.STREAM_F, -1.0, 1.0, halo=0.75)
+            u = np.full(f.shape, -3.0)
+            tickets[s.submit(nx, 1.0 / (max(nx, ny, nz) + 1), 1e-12, 30, f_host=f, u_out=u, ny=ny, nz=nz)] = k
+            us.append(u)
+            fs.append(f)
+        s.drain(timeout_s=120)
+        res = {tickets[r["ticket"]]: r for r in s.poll(64)}
+    for k, (nx, ny, nz) in enumerate(shapes):
+        f = fs[k].copy()
+        f[[0, -1]] = 0.0
+        f[:, [0, -1]] = 0.0
+        f[:, :, [0, -1]] = 0.0
+        h = 1.0 / (max(nx, ny, nz) + 1)
+        if precision == j3d.SERVE_MIXED:
+            uo, ro = oracle.solve_mixed(np.zeros_like(f), f, h, rtol=1e-12, inner=10, max_sweeps=30)
+        else:
+            uo, ro = oracle.solve_plain(np.zeros_like(f), f, h, rtol=1e-12, check_every=10, max_sweeps=30)
+        assert res[k]["sweeps"] == ro.sweeps and rel(res[k]["resid"], ro.resid) <= RESID_RTOL, (k, shapes[k])
+        assert np.array_equal(us[k], uo), (k, shapes[k])
