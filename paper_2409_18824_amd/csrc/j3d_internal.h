@@ -187,7 +187,9 @@ int sum_blocks(long long n);
 hipError_t launch_sum(const double* x, const double* y, long long n, double* partials, double* out,
                       hipStream_t st);
 
-// The 2D Laplace jacobi benchmark: `sweeps` (1, 2, 4 or 8) Jacobi sweeps of
+// Sweeps per launch (16 or 8) of a long run on an nx x ny interior.
+int jacobi2d_sweeps_per_launch(int nx, int ny);
+// The 2D Laplace jacobi benchmark: `sweeps` (1, 2, 4, 8 or 16) Jacobi sweeps of
 // the interior nx x ny of `in` (row stride si) written to `out` (row stride
 // so); in and out hold the same halo.  Skipped when *done != 0.
 hipError_t launch_jacobi2d(int sweeps, const double* in, double* out, int nx, int ny, int si, int so,

@@ -1,11 +1,12 @@
 // jacobi2d_sweeps: the paper's 2D Laplace jacobi benchmark (Sec. "Flang
 // performance comparison") as a library call.
 //
-// nsweeps sweeps run as launches of 8 sweeps (plus 4, 2, 1 for the rest),
-// ping-ponging between the two arrays.  The number of launches is kept at the
-// parity of nsweeps (one launch is split in two when needed), so the result
-// lands in u_a exactly when nsweeps is even, as if the arrays alternated every
-// sweep.  Long runs replay a captured graph of 64 launches.
+// nsweeps sweeps run as launches of 16 or 8 sweeps (jacobi2d_sweeps_per_launch;
+// plus 8, 4, 2, 1 for the rest), ping-ponging between the two arrays.  The
+// number of launches is kept at the parity of nsweeps (one launch is split in
+// two when needed), so the result lands in u_a exactly when nsweeps is even,
+// as if the arrays alternated every sweep.  Long runs replay a captured graph
+// of 64 launches.
 #include <algorithm>
 #include <cstring>
 #include <string>
@@ -17,12 +18,13 @@ using namespace j3d;
 
 namespace {
 
-// Sweeps per launch for nsweeps sweeps, with the launch count's parity equal
-// to nsweeps'.
-std::vector<int> schedule(long long nsweeps) {
-  std::vector<int> v((size_t)(nsweeps / 8), 8);
-  for (int t : {4, 2, 1})
-    if (nsweeps % 8 & t) v.push_back(t);
+// Sweeps per launch for nsweeps sweeps, `per` (16 or 8) in the long run, with
+// the launch count's parity equal to nsweeps'.
+std::vector<int> schedule(long long nsweeps, int per) {
+  std::vector<int> v((size_t)(nsweeps / per), per);
+  const long long rest = nsweeps % per;
+  for (int t : {8, 4, 2, 1})
+    if (rest & t) v.push_back(t);
   if (v.size() % 2 != (size_t)(nsweeps % 2)) {
     // split the last launch of more than one sweep into two halves
     for (size_t i = v.size(); i-- > 0;)
@@ -57,30 +59,31 @@ extern "C" int jacobi2d_sweeps(j3d_array* u_a, j3d_array* u_b, int64_t nsweeps, 
   double* pa = reinterpret_cast<double*>(a.base);
   double* pb = reinterpret_cast<double*>(b.base);
 
-  const std::vector<int> plan = schedule(nsweeps);
+  const int per = jacobi2d_sweeps_per_launch(nx, ny);
+  const std::vector<int> plan = schedule(nsweeps, per);
   size_t i = 0;
   bool in_a = true;  // the current iterate is in u_a
-  // Whole graphs of kGraphLaunches launches of 8 sweeps (the plan starts
-  // with its 8-sweep launches) when there are two or more of them.
-  long long eights = 0;
-  while (eights < (long long)plan.size() && plan[(size_t)eights] == 8) ++eights;
-  if (eights / kGraphLaunches >= 2) {
+  // Whole graphs of kGraphLaunches launches of `per` sweeps (the plan starts
+  // with them) when there are two or more of them.
+  long long whole = 0;
+  while (whole < (long long)plan.size() && plan[(size_t)whole] == per) ++whole;
+  if (whole / kGraphLaunches >= 2) {
     Scratch* s = nullptr;
     J3D_TRY(get_scratch(st, &s));
     std::string key = "jacobi2d";
-    const long long meta[6] = {(long long)(uintptr_t)pa, (long long)(uintptr_t)pb, nx, ny, sa, sb};
+    const long long meta[7] = {per, (long long)(uintptr_t)pa, (long long)(uintptr_t)pb, nx, ny, sa, sb};
     key.append(reinterpret_cast<const char*>(meta), sizeof meta);
     hipGraphExec_t exec = nullptr;
     J3D_TRY(solve_graph(s, key, [&](hipStream_t q) -> int {
       for (long long l = 0; l < kGraphLaunches; ++l) {
         const bool from_a = (l % 2) == 0;
-        J3D_HIP(launch_jacobi2d(8, from_a ? pa : pb, from_a ? pb : pa, nx, ny, from_a ? sa : sb,
+        J3D_HIP(launch_jacobi2d(per, from_a ? pa : pb, from_a ? pb : pa, nx, ny, from_a ? sa : sb,
                                 from_a ? sb : sa, nullptr, q));
       }
       return J3D_OK;
     }, &exec));
-    for (long long g = 0; g < eights / kGraphLaunches; ++g) J3D_HIP(hipGraphLaunch(exec, st));
-    i = (size_t)(eights / kGraphLaunches * kGraphLaunches);
+    for (long long g = 0; g < whole / kGraphLaunches; ++g) J3D_HIP(hipGraphLaunch(exec, st));
+    i = (size_t)(whole / kGraphLaunches * kGraphLaunches);
   }
   for (; i < plan.size(); ++i) {
     J3D_HIP(launch_jacobi2d(plan[i], in_a ? pa : pb, in_a ? pb : pa, nx, ny, in_a ? sa : sb, in_a ? sb : sa,

@@ -89,3 +89,26 @@ def test_jacobi2d_eight_sweep_shapes(shape, dims, monkeypatch):
         torch.cuda.synchronize()
         got = (ua if nsweeps % 2 == 0 else ub).to_numpy2d()[:, : nx + 2]
         assert np.array_equal(got, oracle.jacobi2d(u0, nsweeps)), nsweeps
+
+
+@pytest.mark.parametrize("dims", [(96, 16), (97, 17), (127, 400), (352, 353), (697, 601), (1024, 1000), (1055, 1051),
+                                  (1057, 1060), (1501, 1297), (3, 2000), (2500, 1)])
+def test_jacobi2d_sixteen_sweep_launches(dims):
+    """Launches of 16 sweeps with two columns per lane (3, 4 and 5 rows per
+    wavefront, chosen by the number of tiles) and the 8-sweep launches of the
+    grids past one round of them: odd and even extents, tiles that end on
+    either cell of a pair, random halos; 57 = 3 x 16 + 8 + 1 sweeps, and 16
+    and 24, whose launch counts get their parity by a split launch."""
+    nx, ny = dims
+    say("jacobi2d sixteen", dims)
+    u0 = grid(nx, ny, 6)
+    for nsweeps in (16, 24, 57):
+        ua, ub = j3d.FArray.from_numpy2d(u0), j3d.FArray.from_numpy2d(u0, ld_extra=3)
+        j3d.jacobi2d_sweeps(ua, ub, nsweeps)
+        torch.cuda.synchronize()
+        res, other = (ua, ub) if nsweeps % 2 == 0 else (ub, ua)
+        assert np.array_equal(res.to_numpy2d()[:, : nx + 2], oracle.jacobi2d(u0, nsweeps)), nsweeps
+        # the halo of the array that was not the result is untouched too
+        o = other.to_numpy2d()[:, : nx + 2]
+        assert np.array_equal(o[0], u0[0]) and np.array_equal(o[-1], u0[-1])
+        assert np.array_equal(o[:, 0], u0[:, 0]) and np.array_equal(o[:, -1], u0[:, -1])
