@@ -363,7 +363,8 @@ typedef struct j3d_grid {
  * registers.  variant is a bit set: 1 stages each plane in LDS (else x/y
  * neighbours are read through the cache); 2 and 16 give each thread
  * 2^(bit 2 + 2 x bit 16) consecutive rows (register blocking in y); 4 writes
- * outputs with nontemporal stores (8 is not used).  persistent = 1 launches a
+ * outputs with nontemporal stores, except in passes whose arrays (40 to 256
+ * MB in all) stay in the last-level cache (8 is not used).  persistent = 1 launches a
  * fixed grid of workgroups that stride over the tile list, 0 one workgroup
  * per tile.  order maps dispatch order to tiles: 0 gives each of the 8 XCDs
  * one contiguous block of tiles, 1 keeps the launch order, 2 cuts each z-slab

@@ -183,6 +183,7 @@ void build_tables(const BatchFields& bf, const TileCfg& c, std::vector<GridArgs>
     for (int t = 0; t < 4; ++t) tab[t][g].id = g;
     tile0 += tab[0][g].tiles_x * tab[0][g].tiles_y * tab[0][g].tiles_z;
   }
+  for (int t = 0; t < 4; ++t) set_stream(tab[t].data(), n, J3D_F64);
   *ntiles = tile0;
 }
 
@@ -198,6 +199,7 @@ void build_tables2(const BatchFields& bf, const TileCfg& c2, std::vector<GridArg
     tab2[0][g].id = tab2[1][g].id = g;
     tile0 += tab2[0][g].tiles_x * tab2[0][g].tiles_y * tab2[0][g].tiles_z;
   }
+  for (int t = 0; t < 2; ++t) set_stream(tab2[t].data(), n, J3D_F64);
   *ntiles = tile0;
 }
 
@@ -213,6 +215,7 @@ void build_tables3(const BatchFields& bf, const TileCfg& c3, std::vector<GridArg
     tab3[0][g].id = tab3[1][g].id = g;
     tile0 += tab3[0][g].tiles_x * tab3[0][g].tiles_y * tab3[0][g].tiles_z;
   }
+  for (int t = 0; t < 2; ++t) set_stream(tab3[t].data(), n, J3D_F64);
   *ntiles = tile0;
 }
 

@@ -33,6 +33,8 @@ struct GridArgs {
   int chunk;        // order 2: tiles per XCD chunk
   int wide_planes;  // some plane of an array spans 2^31 bytes or more: the one-sweep
                     // pass takes its pointer-addressed path
+  int stream;       // variants with bit 4 write nontemporally: the pass's arrays overflow
+                    // the last-level cache, or the pass is short (see set_stream)
 };
 
 // Kernel pass flags (compile-time).
@@ -61,7 +63,7 @@ constexpr int kOrderSlots = 3;
 struct TileCfg {
   int rows;       // wavefronts per workgroup
   int planes;     // z-planes per tile
-  int variant;    // bit set: 1 LDS plane; 2, 16 rows per thread; 4 nontemporal stores
+  int variant;    // bit set: 1 LDS plane; 2, 16 rows per thread; 4 nontemporal stores (see GridArgs::stream)
   int persistent; // 1: fixed grid striding over tiles
   int order;      // 0 XCD-blocked, 1 as launched, 2 chunked per XCD within each slab
   int cols;       // wavefronts side by side along x (1, 2 or 4)

@@ -140,6 +140,29 @@ int check_h(double h) {
   return J3D_OK;
 }
 
+// Nontemporal stores pay once the arrays of a pass overflow the 256 MB
+// last-level cache; below that the next pass finds plainly stored lines
+// there, and the tiles' partial lines at either end of a row are merged in
+// L2.  us per pass, plain against nontemporal, best shape of each: FP64
+// three sweeps 200^3 (192 MB) 48.4 / 58.4, 181x143x160 (99 MB) 29.7 / 33.3,
+// 128^3 (50 MB) 20.1 / 21.7, 232^3 (300 MB) 77.4 / 75.1, 256^3 111.3 /
+// 107.5; two sweeps 200^3 39.4 / 48.5, 232^3 69.6 / 65.2; FP32 two sweeps
+// 256^3 (201 MB) 41.7 / 52.0, three 52.8 / 60.8.  Short passes are better off
+// nontemporal again, since the kernel's end waits for the caches to write
+// plain stores back: FP64 three sweeps 96^3 (21 MB) 13.2 / 12.9, 112^3 (34
+// MB) 16.3 / 15.7, FP32 300x40x246 (35 MB) 19.1 / 18.7.
+void set_stream(GridArgs* g, int n, int dtype) {
+  constexpr double kLastLevelCache = 256e6, kShortPass = 40e6;
+  const double es = dtype == J3D_F64 ? 8.0 : 4.0;
+  double bytes = 0.0;
+  for (int q = 0; q < n; ++q) {
+    const double per = (g[q].u ? es : 0) + (g[q].o ? es : 0) + (g[q].f ? es : 0) + (g[q].u64 ? 8.0 : 0) +
+                       (g[q].r32 ? 4.0 : 0);
+    bytes += per * (double)g[q].nx * (double)g[q].ny * (double)g[q].nz;
+  }
+  for (int q = 0; q < n; ++q) g[q].stream = bytes > kLastLevelCache || bytes < kShortPass ? 1 : 0;
+}
+
 GridArgs make_args(const Field* u, const Field* o, const Field* f, const Field* u64,
                    const Field* r32, double h, const TileCfg& c, int tile0) {
   GridArgs g{};
@@ -169,6 +192,7 @@ GridArgs make_args(const Field* u, const Field* o, const Field* f, const Field* 
   g.h2f = static_cast<float>(h * h);
   g.order = c.order;
   g.chunk = (g.tiles_x * g.tiles_y + 7) / 8;
+  set_stream(&g, 1, any->dtype);
   // the buffer-addressed one-sweep path needs every plane (interior and
   // halo) under 2^31 bytes
   const Field* fs[5] = {u, o, f, u64, r32};

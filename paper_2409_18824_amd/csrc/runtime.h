@@ -69,6 +69,10 @@ GridArgs make_args2(const Field* u, const Field* o, const Field* f, const Field*
 GridArgs make_args3(const Field* u, const Field* o, const Field* f, const Field* u64, double h,
                     const TileCfg& c, int tile0);
 
+// Sets GridArgs::stream of the n grids that one pass of element type dtype
+// covers (make_args* set it for a grid swept alone).
+void set_stream(GridArgs* g, int n, int dtype);
+
 // Default tile shape for a grid of this size and element type (the
 // autotuner's cached choice when there is one).
 TileCfg default_cfg(int dtype, int nx, int ny, int nz);

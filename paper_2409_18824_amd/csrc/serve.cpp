@@ -418,6 +418,8 @@ int queue_cycle(j3d_server* s, const std::vector<Slot*>& slots) {
     fit3 = fit3 && plane_fits_u32(L.u) && plane_fits_u32(L.r32) && plane_fits_u32(L.e0) && plane_fits_u32(L.e1);
     ++n_in;
   }
+  set_stream(T[K_DEF], n, J3D_F64);
+  for (int k = K_FIRST1; k < K_NKINDS; ++k) set_stream(T[k], n_in, J3D_F32);
   if ((size_t)nt_def > s->part_cap) {
     J3D_HIP(hipStreamSynchronize(s->st));
     if (s->d_part) J3D_HIP(hipFree(s->d_part));
@@ -517,6 +519,9 @@ int queue_cycle64(j3d_server* s, const std::vector<Slot*>& slots) {
     fit3 = fit3 && plane_fits_u32(L.u) && plane_fits_u32(L.w) && plane_fits_u32(L.f);
     ++n_in;
   }
+  set_stream(T[K_DEF], n, J3D_F64);
+  for (auto& kind : kP64)
+    for (int k : kind) set_stream(T[k], n_in, J3D_F64);
   if ((size_t)nt_def > s->part_cap) {
     J3D_HIP(hipStreamSynchronize(s->st));
     if (s->d_part) J3D_HIP(hipFree(s->d_part));

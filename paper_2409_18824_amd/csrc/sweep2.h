@@ -180,7 +180,7 @@ __device__ __forceinline__ void sweep2_tile(const GridArgs& g, int t, double* __
               double* q = u64 + co[r] + g.s64_z * (k - 1);
               q[0] = q[0] + static_cast<double>(u2);
             } else {
-              put<T, NT>(out + co[r] + g.so_z * (k - 1), u2);
+              put<T, NT>(out + co[r] + g.so_z * (k - 1), u2, g.stream != 0);
             }
           }
         }

@@ -192,7 +192,7 @@ __device__ __forceinline__ void sweep3_tile(const GridArgs& g, int t, double* __
         if (FL & F_LAST)
           bstore<double, false>(pq[r] + static_cast<double>(st[r]), ro, oo[r]);
         else
-          bstore<T, NT>(st[r], ro, oo[r]);
+          bstore<T, NT>(st[r], ro, oo[r], g.stream != 0);
       }
     }
   };
