@@ -424,9 +424,8 @@ static hipError_t dispatch(int dtype, unsigned flags, const sweep_detail::Launch
 }
 
 // The variant a one-sweep pass of this grid runs: without nontemporal stores
-// when the pass stays in the caches.  (A variant of its own and not a test
-// of GridArgs::stream as in the multi-sweep passes: around the two-plane
-// tiles' stores the test cost 4 % at 64^3.)
+// when the pass stays in the caches.  (A test of GridArgs::stream around the
+// stores cost 4 % at 64^3.)
 static TileCfg one_sweep_cfg(const TileCfg& c, const GridArgs& g) {
   TileCfg k = c;
   if (g.stream == 0 && c.cols == 1) k.variant &= ~4;

@@ -79,10 +79,9 @@ __device__ __forceinline__ double h2_of<double>(const GridArgs& g) { return g.h2
 template <>
 __device__ __forceinline__ float h2_of<float>(const GridArgs& g) { return g.h2f; }
 
-// Store; NT and stream: streamed past the caches (nontemporal).
 template <typename T, bool NT>
-__device__ __forceinline__ void put(T* p, T v, bool stream = true) {
-  if (NT && stream)
+__device__ __forceinline__ void put(T* p, T v) {
+  if (NT)
     __builtin_nontemporal_store(v, p);
   else
     *p = v;
@@ -187,20 +186,13 @@ __device__ __forceinline__ float bload<float>(__amdgpu_buffer_rsrc_t r, uint32_t
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
 
-// Store; NT and stream: past the caches (cache policy "nt").
+// Store; NT streams it past the caches (cache policy "nt").
 template <typename T, bool NT>
-__device__ __forceinline__ void bstore(T v, __amdgpu_buffer_rsrc_t r, uint32_t off, bool stream = true) {
-  if (NT && stream) {
-    if constexpr (sizeof(T) == 8)
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(buf_u2, v), r, off, 0, 2);
-    else
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, 2);
-  } else {
-    if constexpr (sizeof(T) == 8)
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(buf_u2, v), r, off, 0, 0);
-    else
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, 0);
-  }
+__device__ __forceinline__ void bstore(T v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
+  if constexpr (sizeof(T) == 8)
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(buf_u2, v), r, off, 0, NT ? 2 : 0);
+  else
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, NT ? 2 : 0);
 }
 
 // Rows per thread encoded in the variant bits 2 and 16.

@@ -36,7 +36,7 @@ namespace sweep_detail {
 // Output columns per tile in x (one wavefront along x).
 constexpr int sweep2_cols(int wx) { return wx == 1 ? WAVE - 4 : 0; }
 
-template <typename T, int BY, int WX, int VAR>
+template <typename T, int BY, int WX>
 struct Smem2 {
   T edge[3][BY][2][WAVE];   // plane slot, wavefront, first/last row of u1
   T u0edge[2][BY][2][WAVE]; // plane parity, wavefront, first/last row of u0
@@ -48,8 +48,8 @@ struct Smem2 {
 // cycle), F_LAST (add (double) u2 to g.u64 instead of storing it; the last
 // two sweeps of a correction cycle).
 template <typename T, int BY, int WX, int VAR, unsigned FL>
-__device__ __forceinline__ void sweep2_tile(const GridArgs& g, int t, double* __restrict__ partials,
-                                            Smem2<T, BY, WX, VAR>& sm) {
+__device__ __forceinline__ void sweep2_march(const GridArgs& g, int t, double* __restrict__ partials,
+                                             Smem2<T, BY, WX>& sm) {
   static_assert(WX == 1, "the two-sweep pass uses one wavefront along x");
   constexpr int RY = rows_per_thread(VAR);
   constexpr int TR = BY * RY;   // block rows
@@ -180,7 +180,7 @@ __device__ __forceinline__ void sweep2_tile(const GridArgs& g, int t, double* __
               double* q = u64 + co[r] + g.s64_z * (k - 1);
               q[0] = q[0] + static_cast<double>(u2);
             } else {
-              put<T, NT>(out + co[r] + g.so_z * (k - 1), u2, g.stream != 0);
+              put<T, NT>(out + co[r] + g.so_z * (k - 1), u2);
             }
           }
         }
@@ -203,11 +203,21 @@ __device__ __forceinline__ void sweep2_tile(const GridArgs& g, int t, double* __
   __syncthreads();
 }
 
+// The tile with or without nontemporal stores (see GridArgs::stream).
+template <typename T, int BY, int WX, int VAR, unsigned FL>
+__device__ __forceinline__ void sweep2_tile(const GridArgs& g, int t, double* __restrict__ partials,
+                                            Smem2<T, BY, WX>& sm) {
+  if ((VAR & 4) != 0 && g.stream == 0)
+    sweep2_march<T, BY, WX, (VAR & ~4), FL>(g, t, partials, sm);
+  else
+    sweep2_march<T, BY, WX, VAR, FL>(g, t, partials, sm);
+}
+
 template <typename T, int BY, int WX, int VAR, unsigned FL>
 __global__ void __launch_bounds__(WAVE * WX * BY)
     k_sweep2_one(GridArgs g, double* __restrict__ partials, const int* __restrict__ done) {
   if (done != nullptr && *done != 0) return;
-  __shared__ Smem2<T, BY, WX, VAR> sm;
+  __shared__ Smem2<T, BY, WX> sm;
   const int ntiles = g.tiles_x * g.tiles_y * g.tiles_z;
   if (g.order == 0) {
     for (int t = xcd_remap(blockIdx.x, gridDim.x); t < ntiles; t += gridDim.x)
@@ -226,7 +236,7 @@ template <typename T, int BY, int WX, int VAR, unsigned FL>
 __global__ void __launch_bounds__(WAVE * WX * BY)
     k_sweep2_batch(const GridArgs* __restrict__ table, int ngrids, int ntiles,
                    double* __restrict__ partials, const int* __restrict__ done, int order, int chunk) {
-  __shared__ Smem2<T, BY, WX, VAR> sm;
+  __shared__ Smem2<T, BY, WX> sm;
   const int nv = order == 0 ? ntiles : virtual_tiles(ntiles, order, chunk);
   const int first = order == 0 ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   for (int vb = first; vb < nv; vb += gridDim.x) {

@@ -81,8 +81,8 @@ __device__ __forceinline__ float shift_in_right(float v) {
 // step k, before its arithmetic, so a whole step of work covers their
 // latency; one extra plane of registers per streamed array holds them.
 template <typename T, int BY, int VAR, unsigned FL>
-__device__ __forceinline__ void sweep3_tile(const GridArgs& g, int t, double* __restrict__ partials,
-                                            Smem3<T, BY>& sm) {
+__device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* __restrict__ partials,
+                                             Smem3<T, BY>& sm) {
   constexpr int RY = rows_per_thread(VAR);
   constexpr int TR = BY * RY;  // block rows
   constexpr int W = kSweep3Cols;
@@ -192,7 +192,7 @@ __device__ __forceinline__ void sweep3_tile(const GridArgs& g, int t, double* __
         if (FL & F_LAST)
           bstore<double, false>(pq[r] + static_cast<double>(st[r]), ro, oo[r]);
         else
-          bstore<T, NT>(st[r], ro, oo[r], g.stream != 0);
+          bstore<T, NT>(st[r], ro, oo[r]);
       }
     }
   };
@@ -377,6 +377,17 @@ __device__ __forceinline__ void sweep3_tile(const GridArgs& g, int t, double* __
     if (wy == 0 && lane == 0) partials[g.tile0 + t] = tot;
   }
   __syncthreads();
+}
+
+// The tile with or without nontemporal stores (see GridArgs::stream): two
+// bodies, since a test around each plane's stores cost 0.7 % of a batch.
+template <typename T, int BY, int VAR, unsigned FL>
+__device__ __forceinline__ void sweep3_tile(const GridArgs& g, int t, double* __restrict__ partials,
+                                            Smem3<T, BY>& sm) {
+  if ((VAR & 4) != 0 && g.stream == 0)
+    sweep3_march<T, BY, (VAR & ~4), FL>(g, t, partials, sm);
+  else
+    sweep3_march<T, BY, VAR, FL>(g, t, partials, sm);
 }
 
 template <typename T, int BY, int VAR, unsigned FL>
