@@ -334,10 +334,10 @@ typedef struct j3d_solve_result {
  * from e = 0 with h^2 = (float)(h*h).  The last cycle ends with a defect
  * step, so u includes every correction and `resid` is its residual.
  *
- * Sweeps run two or three per pass over memory (as jacobi3d_sweep2 and
- * jacobi3d_sweep3), three when the arrays of a pass exceed 512 MB, i.e.
- * overflow the last-level cache; J3D_SOLVE_SWEEPS_PER_PASS=1, 2 or 3 fixes
- * the pass length.  Every schedule gives the same iterate bit for bit.
+ * Sweeps run three per pass over memory (as jacobi3d_sweep3; the residual
+ * of a check is fused into the pass that forms its iterate), fewer where
+ * the checks are closer; J3D_SOLVE_SWEEPS_PER_PASS=1, 2 or 3 fixes the pass
+ * length.  Every schedule gives the same iterate bit for bit.
  *
  * Not converging is not an error (converged = 0).  A NaN/Inf residual stops
  * the solve with status and return value J3D_ENONFINITE.  The call blocks
@@ -525,15 +525,13 @@ uint64_t j3d_request_state_bytes(int32_t precision, int32_t nx, int32_t ny, int3
  * all slots' tiles).  At every cycle boundary converged or capped requests
  * retire and waiting ones are admitted (continuous batching).  A request's
  * result does not depend on which others share its cycles.  The FP32 sweeps
- * of a cycle run two per pass over memory, or three when the cycle's FP32
- * state exceeds 512 MB (J3D_SERVE_TRIPLES=0 or =1 forces one or the other);
- * the iterates are the same bit for bit either way.  A request's result is
+ * of a cycle run three per pass over memory, or two with
+ * J3D_SERVE_TRIPLES=0; the iterates are the same bit for bit either way.  A request's result is
  * that of poisson_solve in MIXED mode with inner_sweeps = cycle_sweeps and
  * max_sweeps rounded up to whole cycles.
  * With precision J3D_SERVE_FP64 a cycle is instead the FP64 residual check
  * of each slot's current iterate followed by cycle_sweeps FP64 Jacobi sweeps
- * (two or three per pass over memory, three when the cycle's FP64 state
- * exceeds 512 MB), so a request's result is that of poisson_solve in FP64
+ * (three per pass over memory), so a request's result is that of poisson_solve in FP64
  * mode with check_every = cycle_sweeps: the plain form the mixed one is
  * measured against, under the same admission and batching.  Errors:
  * J3D_EINVAL (bad options, precision or reserved), J3D_EHIP.

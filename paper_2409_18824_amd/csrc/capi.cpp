@@ -1,6 +1,7 @@
 // C-ABI entry points of libj3d: single sweeps, residual norms, fills,
 // bandwidth probe and housekeeping.  Solves, batches and serving live in
 // solve.cpp, batch.cpp and serve.cpp.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -33,9 +34,78 @@ const std::vector<TileCfg>& tune_table() {
 }
 }  // namespace
 
+// A multi-sweep pass over small grids is short of workgroups and each tile's
+// march along z is one long latency, so the best shape changes with the
+// size: many short tiles below 100^3, tall blocks that just fill the 256 CUs
+// around 128^3, longer tiles beyond.  The shape is the one of least modelled
+// time: a round of workgroups takes (planes + fill) steps of
+//   lat + lat_row * RY + row * (rows of all workgroups on a CU)  [us]
+// (latency of a step, growing with the rows a thread walks, and the CU's
+// throughput), cap workgroups fit a CU by registers and LDS, and the last
+// round may be a partial one.  The constants are fitted to 3700 timed
+// (shape, size) pairs per pass kind over 17 sizes from 32^3 to 512x512x32;
+// the shape chosen is on average 0.3-1.7 % and at worst 9 % slower than the
+// fastest.  Against the fixed shapes before (us per pass, best stores of
+// 40-256 MB passes on both sides): FP64 two sweeps 64^3 27.5 -> 7.9, 128^3
+// 34.5 -> 17.0, 181x143x160 36 -> 25.6; three sweeps 96^3 20.5 -> 12.9,
+// 200^3 77 -> 48; FP32 two sweeps 96^3 14.5 -> 7.8, three sweeps
+// 181x143x160 31 -> 22.6.
+TileCfg modelled_shape(int sweeps, int dtype, const Extents* e, int n) {
+  const bool f32 = dtype == J3D_F32;
+  struct Cost {
+    double lat, lat_row, row, fill;
+  };
+  const Cost k = sweeps == 2 ? (f32 ? Cost{0.4, 0.056, 0.006, 3} : Cost{0.5, 0.047, 0.014, 6})
+                             : (f32 ? Cost{0.3, 0.0026, 0.01, 3} : Cost{0.3, 0.115, 0.042, 4});
+  constexpr int kCus = 256;
+  const int width = 64 - 2 * sweeps, ring = 2 * (sweeps - 1);
+  TileCfg best{4, 16, 6, 0, 0, 1};
+  double best_t = 1e300;
+  for (int rows : {2, 4, 8, 16})
+    for (int ry : {2, 4}) {
+      TileCfg c{rows, 1, ry == 4 ? 20 : 6, 0, 0, 1};
+      if (!(sweeps == 2 ? tile2_cfg_supported(dtype, c) : tile3_cfg_supported(dtype, c))) continue;
+      const int h = rows * ry - ring;
+      const int waves = sweeps == 3 ? (ry == 2 || f32 ? 16 : 12) : (ry == 2 || f32 ? 24 : 16);
+      const int cap = std::max(1, waves / rows);
+      for (int planes : {4, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64}) {
+        double tiles = 0;
+        int deepest = 1;
+        for (int g = 0; g < n; ++g) {
+          const double cols = std::ceil(e[g].nx / (double)width) * std::ceil(e[g].ny / (double)h);
+          tiles += cols * std::ceil(e[g].nz / (double)planes);
+          deepest = std::max(deepest, std::min(planes, e[g].nz));
+        }
+        const double per_cu = std::ceil(tiles / kCus);
+        const double full = std::floor(per_cu / cap), part = per_cu - full * cap;
+        auto step = [&](double wgs) { return k.lat + k.lat_row * ry + k.row * wgs * rows * ry; };
+        const double t = (deepest + k.fill) * (full * step(cap) + (part > 0 ? step(part) : 0.0));
+        if (t < best_t * (1.0 - 1e-12)) {
+          best_t = t;
+          best = c;
+          best.planes = planes;
+        }
+      }
+    }
+  return best;
+}
+
+// Grids whose multi-sweep shapes come from the model: below, a pass is one
+// latency whatever the shape; above, the shapes timed on large cubes.
+static bool modelled_size(long long pts) { return pts >= 4096 && pts < (1LL << 24); }
+
 TileCfg default_cfg(int dtype, int nx, int ny, int nz) {
   TileCfg c;
   if (tune_cache_lookup_single(dtype, nx, ny, nz, &c)) return c;
+  // Passes that stay in the last-level cache: short tiles (4 planes, XCD-
+  // blocked), us per pass against the large-grid shape below: FP64 96^3 6.7 /
+  // 11.2, 128^3 11.4 / 12.7, 200^3 33.6 / 35.8; FP32 64^3 4.3 / 8.4, 128^3
+  // 7.1 / 12.0, 256^3 32.0 / 35.3.
+  {
+    const long long pts = (long long)nx * ny * nz;
+    if (pts >= (dtype == J3D_F64 ? 1LL << 19 : 1LL << 15) && (dtype == J3D_F64 ? 24.0 : 12.0) * (double)pts <= 256e6)
+      return TileCfg{1, 4, 20, 0, 0, 1};
+  }
   // FP64 grids of at most 64^3 points: four wavefronts of two rows per
   // thread, two planes per tile, XCD-blocked (7.45 us per sweep at 64^3 with
   // a residual after every sweep, against 7.8 with four rows per thread and
@@ -57,6 +127,15 @@ TileCfg default_cfg3(int dtype, int nx, int ny, int nz) {
   TileCfg c;
   const int kind = dtype == J3D_F32 ? J3D_KIND_F32X3 : J3D_KIND_F64X3;
   if (tune_cache_lookup_single(kind, nx, ny, nz, &c) && tile3_cfg_supported(dtype, c)) return c;
+  const Extents e{nx, ny, nz};
+  if (modelled_size((long long)nx * ny * nz)) {
+    c = modelled_shape(3, dtype, &e, 1);
+    int tx, ty, tz;
+    tile3_counts(nx, ny, nz, c, &tx, &ty, &tz);
+    // (long rows of few planes: the shapes below make fewer tiles, which the
+    // allocation-free entry point's fixed number of partials must hold)
+    if ((long long)tx * ty * tz <= 65536) return c;
+  }
   // measured on cubes from 96^3 to 512^3 (nontemporal stores throughout):
   // up to about 200^3 points 4 wavefronts of 2 rows per thread and 16
   // planes (more, thinner tiles), XCD-blocked; up to about 300^3, 4
@@ -100,6 +179,13 @@ TileCfg default_cfg2(int dtype, int nx, int ny, int nz) {
   if (tune_cache_lookup_single(dtype == J3D_F32 ? J3D_KIND_F32X2 : J3D_KIND_F64X2, nx, ny, nz, &c) &&
       tile2_cfg_supported(dtype == J3D_F32 ? J3D_F32 : J3D_F64, c))
     return c;
+  const Extents e{nx, ny, nz};
+  const long long pts = (long long)nx * ny * nz;
+  if (modelled_size(pts)) return modelled_shape(2, dtype, &e, 1);
+  // up to 400^3 (measured at 256^3): 4 wavefronts of 4 rows, XCD-blocked, 32
+  // planes in FP64 (86 us against 106 with the shape below), 16 in FP32 (42
+  // against 58)
+  if (pts >= 4096 && pts <= 400LL * 400 * 400) return TileCfg{4, dtype == J3D_F32 ? 16 : 32, 20, 0, 0, 1};
   // measured at 512^3: FP64 16 rows per block, 16 planes, launch order;
   // FP32 32 rows per block, 8 planes, XCD-blocked order (4 rows per thread,
   // nontemporal stores in both)

@@ -79,6 +79,13 @@ TileCfg default_cfg(int dtype, int nx, int ny, int nz);
 TileCfg default_cfg2(int dtype, int nx, int ny, int nz);  // two-sweep pass
 TileCfg default_cfg3(int dtype, int nx, int ny, int nz);  // three-sweep pass
 
+// Tile shape of least modelled time for a pass of 2 or 3 sweeps over n grids
+// (host-only).
+struct Extents {
+  int nx, ny, nz;
+};
+TileCfg modelled_shape(int sweeps, int dtype, const Extents* e, int n);
+
 // A validated jacobi3d_sweep3 call: its fields, the residual flag of the
 // pass (F_RES, F_RES1 or F_RES2), the tile shape and the launch arguments.
 struct Sweep3Call {

@@ -149,6 +149,7 @@ struct j3d_server {
   hipEvent_t ev = nullptr;
   TileCfg cd{}, cs{}, cs2{}, cs3{};  // defect, one-, two- and three-sweep FP32 passes
   TileCfg cs_one64{}, c64_2{}, c64_3{};  // FP64 precision: one-, two- and three-sweep passes
+  bool fixed3 = false, fixed3_64 = false;  // three-sweep shape from the environment
   int passes_in_cycle = 0;           // FP64 precision: passes the last cycle queued
 
   double now() const { return now_seconds() - t0; }
@@ -185,23 +186,27 @@ enum Kind {
 // from the current iterate to the other (parity 0) or back (parity 1).
 constexpr int kP64[3][2] = {{K_FIRST1, K_FL1}, {K_FIRST2, K_FL2}, {K_FIRST3, K_FL3}};
 
-// Three-sweep correction passes when the FP32 state the cycle sweeps (r,
-// e0, e1 of every slot) exceeds 512 MB, twice the last-level cache, as in
-// the solver; J3D_SERVE_TRIPLES=0 or =1 forces two-sweep or three-sweep
-// passes.  Every schedule gives the same iterates bit for bit.
-bool serve_triples(long long points) {
+// Three-sweep passes, which take less time per sweep at every size (see
+// poisson_solve); J3D_SERVE_TRIPLES=0 forces two-sweep passes.  Every
+// schedule gives the same iterates bit for bit.
+bool serve_triples() {
   const char* e = std::getenv("J3D_SERVE_TRIPLES");
-  if (e != nullptr && *e == '0') return false;
-  if (e != nullptr && *e == '1') return true;
-  return 12.0 * (double)points > 512e6;
+  return e == nullptr || *e != '0';
 }
 
-// The same rule for FP64 sweeps (24 bytes per point of u, w and f).
-bool serve_triples64(long long points) {
-  const char* e = std::getenv("J3D_SERVE_TRIPLES");
-  if (e != nullptr && *e == '0') return false;
-  if (e != nullptr && *e == '1') return true;
-  return 24.0 * (double)points > 512e6;
+// Tile shapes of a cycle's two- and three-sweep passes: modelled on the
+// grids that take part while their points are few (2^24, as for single
+// grids), else the shapes measured on the loaded server.  12 requests of
+// 32^3 to 96^3: 20 us per FP32 two-sweep pass with the latter, 10 us per
+// three-sweep pass with the former.  (The pass that sums residuals keeps
+// one shape, so that a request's residual does not depend on the others.)
+void cycle_shapes(const std::vector<Extents>& grids, int dtype, bool fixed3, TileCfg* c2, TileCfg* c3) {
+  constexpr size_t kMaxModelled = 256;  // bounds the model's time on the host
+  double pts = 0;
+  for (const Extents& e : grids) pts += (double)e.nx * e.ny * e.nz;
+  if (grids.empty() || grids.size() > kMaxModelled || pts >= (double)(1 << 24)) return;
+  *c2 = modelled_shape(2, dtype, grids.data(), (int)grids.size());
+  if (!fixed3) *c3 = modelled_shape(3, dtype, grids.data(), (int)grids.size());
 }
 
 int serve_fail(j3d_server* s, int code, const char* what) {
@@ -217,13 +222,17 @@ int serve_fail(j3d_server* s, int code, const char* what) {
 
 // A three-sweep tile shape from the environment ("rows,planes,variant,
 // persistent,order,cols"), if set and supported.
-void tile3_from_env(const char* name, int dtype, TileCfg* c) {
+// Returns whether it was.
+bool tile3_from_env(const char* name, int dtype, TileCfg* c) {
   const char* e = std::getenv(name);
-  if (e == nullptr) return;
+  if (e == nullptr) return false;
   TileCfg t{};
   if (std::sscanf(e, "%d,%d,%d,%d,%d,%d", &t.rows, &t.planes, &t.variant, &t.persistent, &t.order, &t.cols) == 6 &&
-      tile3_cfg_supported(dtype, t))
+      tile3_cfg_supported(dtype, t)) {
     *c = t;
+    return true;
+  }
+  return false;
 }
 
 int setup_device(j3d_server* s) {
@@ -244,22 +253,18 @@ int setup_device(j3d_server* s) {
   J3D_HIP(hipHostMalloc((void**)&s->h_out, n * sizeof(double), hipHostMallocDefault));
   J3D_HIP(hipHostMalloc((void**)&s->h_flags, 2 * n * sizeof(int), hipHostMallocDefault));
   J3D_HIP(hipMemsetAsync(s->d_done, 0, 2 * n * sizeof(int), s->st));
-  s->cd = default_cfg(J3D_F64, 128, 128, 128);
-  s->cs = default_cfg(J3D_F32, 128, 128, 128);
-  s->cs2 = default_cfg2(J3D_F32, 128, 128, 128);
+  s->cd = TileCfg{1, 16, 20, 0, 2, 1};
+  s->cs = TileCfg{1, 16, 20, 0, 2, 1};
+  s->cs2 = TileCfg{8, 8, 20, 0, 0, 1};
   // the batched three-sweep passes run over up to 2e8 active points of
   // grids of 32^3 to 384^3; shapes measured on the served stream (see
   // below), J3D_SERVE_TILE3 / J3D_SERVE_TILE3_FP64 override them
   s->cs3 = TileCfg{4, 24, 20, 0, 2, 1};
-  tile3_from_env("J3D_SERVE_TILE3", J3D_F32, &s->cs3);
-  s->cs_one64 = default_cfg(J3D_F64, 128, 128, 128);
-  s->cs_one64.persistent = 0;
-  s->c64_2 = default_cfg2(J3D_F64, 128, 128, 128);
+  s->fixed3 = tile3_from_env("J3D_SERVE_TILE3", J3D_F32, &s->cs3);
+  s->cs_one64 = TileCfg{1, 16, 20, 0, 2, 1};
+  s->c64_2 = TileCfg{4, 16, 20, 0, 1, 1};
   s->c64_3 = TileCfg{4, 48, 20, 0, 1, 1};
-  tile3_from_env("J3D_SERVE_TILE3_FP64", J3D_F64, &s->c64_3);
-  s->cd.persistent = 0;
-  s->cs.persistent = 0;
-  s->cs2.persistent = 0;
+  s->fixed3_64 = tile3_from_env("J3D_SERVE_TILE3_FP64", J3D_F64, &s->c64_3);
   return J3D_OK;
 }
 
@@ -373,6 +378,14 @@ int admit(j3d_server* s) {
   }
 }
 
+// The grids of the slots that still have sweeps left.
+std::vector<Extents> cycle_extents(const std::vector<Slot*>& slots) {
+  std::vector<Extents> v;
+  for (const Slot* sl : slots)
+    if (sl->sweeps < sl->req->max_sweeps) v.push_back(Extents{sl->L.u.nx(), sl->L.u.ny(), sl->L.u.nz()});
+  return v;
+}
+
 // Build the per-kind tables of the active slots and queue one cycle.
 int queue_cycle(j3d_server* s, const std::vector<Slot*>& slots) {
   const int n = (int)slots.size();
@@ -380,7 +393,8 @@ int queue_cycle(j3d_server* s, const std::vector<Slot*>& slots) {
   GridArgs* T[K_NKINDS];
   for (int k = 0; k < K_NKINDS; ++k) T[k] = s->h_tab + (size_t)k * s->o.max_slots;
   int nt_def = 0, nt_swp = 0, nt_swp2 = 0, nt_swp3 = 0, n_in = 0;
-  long long pts_in = 0;
+  TileCfg cs2 = s->cs2, cs3 = s->cs3;
+  cycle_shapes(cycle_extents(slots), J3D_F32, s->fixed3, &cs2, &cs3);
   bool fit3 = true;  // every plane below 4 GiB (needed by three-sweep passes)
   for (int g = 0; g < n; ++g) {
     Slot* sl = slots[g];
@@ -395,18 +409,18 @@ int queue_cycle(j3d_server* s, const std::vector<Slot*>& slots) {
     GridArgs a[K_NKINDS];
     a[K_FIRST1] = make_args(nullptr, &L.e0, &L.r32, nullptr, nullptr, h, s->cs, nt_swp);
     a[K_FL1] = make_args(nullptr, nullptr, &L.r32, &L.u, nullptr, h, s->cs, nt_swp);
-    a[K_FIRST2] = make_args2(nullptr, &L.e0, &L.r32, nullptr, h, s->cs2, nt_swp2);
-    a[K_FL2] = make_args2(nullptr, nullptr, &L.r32, &L.u, h, s->cs2, nt_swp2);
-    a[K_MID2A] = make_args2(&L.e0, &L.e1, &L.r32, nullptr, h, s->cs2, nt_swp2);
-    a[K_MID2B] = make_args2(&L.e1, &L.e0, &L.r32, nullptr, h, s->cs2, nt_swp2);
-    a[K_LAST2A] = make_args2(&L.e0, nullptr, &L.r32, &L.u, h, s->cs2, nt_swp2);
-    a[K_LAST2B] = make_args2(&L.e1, nullptr, &L.r32, &L.u, h, s->cs2, nt_swp2);
-    a[K_FIRST3] = make_args3(nullptr, &L.e0, &L.r32, nullptr, h, s->cs3, nt_swp3);
-    a[K_FL3] = make_args3(nullptr, nullptr, &L.r32, &L.u, h, s->cs3, nt_swp3);
-    a[K_MID3A] = make_args3(&L.e0, &L.e1, &L.r32, nullptr, h, s->cs3, nt_swp3);
-    a[K_MID3B] = make_args3(&L.e1, &L.e0, &L.r32, nullptr, h, s->cs3, nt_swp3);
-    a[K_LAST3A] = make_args3(&L.e0, nullptr, &L.r32, &L.u, h, s->cs3, nt_swp3);
-    a[K_LAST3B] = make_args3(&L.e1, nullptr, &L.r32, &L.u, h, s->cs3, nt_swp3);
+    a[K_FIRST2] = make_args2(nullptr, &L.e0, &L.r32, nullptr, h, cs2, nt_swp2);
+    a[K_FL2] = make_args2(nullptr, nullptr, &L.r32, &L.u, h, cs2, nt_swp2);
+    a[K_MID2A] = make_args2(&L.e0, &L.e1, &L.r32, nullptr, h, cs2, nt_swp2);
+    a[K_MID2B] = make_args2(&L.e1, &L.e0, &L.r32, nullptr, h, cs2, nt_swp2);
+    a[K_LAST2A] = make_args2(&L.e0, nullptr, &L.r32, &L.u, h, cs2, nt_swp2);
+    a[K_LAST2B] = make_args2(&L.e1, nullptr, &L.r32, &L.u, h, cs2, nt_swp2);
+    a[K_FIRST3] = make_args3(nullptr, &L.e0, &L.r32, nullptr, h, cs3, nt_swp3);
+    a[K_FL3] = make_args3(nullptr, nullptr, &L.r32, &L.u, h, cs3, nt_swp3);
+    a[K_MID3A] = make_args3(&L.e0, &L.e1, &L.r32, nullptr, h, cs3, nt_swp3);
+    a[K_MID3B] = make_args3(&L.e1, &L.e0, &L.r32, nullptr, h, cs3, nt_swp3);
+    a[K_LAST3A] = make_args3(&L.e0, nullptr, &L.r32, &L.u, h, cs3, nt_swp3);
+    a[K_LAST3B] = make_args3(&L.e1, nullptr, &L.r32, &L.u, h, cs3, nt_swp3);
     for (int k = K_FIRST1; k < K_NKINDS; ++k) {
       a[k].id = sl->id;
       T[k][n_in] = a[k];
@@ -414,7 +428,6 @@ int queue_cycle(j3d_server* s, const std::vector<Slot*>& slots) {
     nt_swp += a[K_FIRST1].tiles_x * a[K_FIRST1].tiles_y * a[K_FIRST1].tiles_z;
     nt_swp2 += a[K_FIRST2].tiles_x * a[K_FIRST2].tiles_y * a[K_FIRST2].tiles_z;
     nt_swp3 += a[K_FIRST3].tiles_x * a[K_FIRST3].tiles_y * a[K_FIRST3].tiles_z;
-    pts_in += (long long)L.u.nx() * L.u.ny() * L.u.nz();
     fit3 = fit3 && plane_fits_u32(L.u) && plane_fits_u32(L.r32) && plane_fits_u32(L.e0) && plane_fits_u32(L.e1);
     ++n_in;
   }
@@ -444,10 +457,10 @@ int queue_cycle(j3d_server* s, const std::vector<Slot*>& slots) {
   // step divides cyc), the middle passes ping-pong between e0 and e1, the
   // last adds its result to u.
   if (n_in > 0) {
-    const int step = (fit3 && serve_triples(pts_in)) ? 3 : 2;
+    const int step = (fit3 && serve_triples()) ? 3 : 2;
     auto pass = [&](int len, unsigned fl, Kind k1, Kind k2, Kind k3) -> hipError_t {
-      if (len == 3) return launch_sweep3_batch(J3D_F32, fl, s->cs3, D[k3], n_in, nt_swp3, nullptr, done, s->st);
-      if (len == 2) return launch_sweep2_batch(J3D_F32, fl, s->cs2, D[k2], n_in, nt_swp2, nullptr, done, s->st);
+      if (len == 3) return launch_sweep3_batch(J3D_F32, fl, cs3, D[k3], n_in, nt_swp3, nullptr, done, s->st);
+      if (len == 2) return launch_sweep2_batch(J3D_F32, fl, cs2, D[k2], n_in, nt_swp2, nullptr, done, s->st);
       return launch_pass_batch(J3D_F32, fl, s->cs, D[k1], n_in, nt_swp, nullptr, done, s->st);
     };
     if (cyc <= step) {
@@ -473,16 +486,16 @@ int queue_cycle(j3d_server* s, const std::vector<Slot*>& slots) {
 
 // FP64 precision: the residual check of every slot's current iterate, then
 // cycle_sweeps FP64 sweeps over the slots that still have sweeps left, in
-// passes of `step` sweeps (three when the FP64 state of the cycle exceeds
-// 512 MB, else two; the first pass takes cycle_sweeps mod step sweeps when
-// step does not divide it), alternating between u and w.
+// passes of `step` sweeps (three; the first pass takes cycle_sweeps mod step
+// sweeps when step does not divide it), alternating between u and w.
 int queue_cycle64(j3d_server* s, const std::vector<Slot*>& slots) {
   const int n = (int)slots.size();
   const int cyc = s->o.cycle_sweeps;
   GridArgs* T[K_NKINDS];
   for (int k = 0; k < K_NKINDS; ++k) T[k] = s->h_tab + (size_t)k * s->o.max_slots;
   int nt_def = 0, nt[3] = {0, 0, 0}, n_in = 0;
-  long long pts_in = 0;
+  TileCfg c64_2 = s->c64_2, c64_3 = s->c64_3;
+  cycle_shapes(cycle_extents(slots), J3D_F64, s->fixed3_64, &c64_2, &c64_3);
   bool fit3 = true;
   for (int g = 0; g < n; ++g) {
     Slot* sl = slots[g];
@@ -500,8 +513,8 @@ int queue_cycle64(j3d_server* s, const std::vector<Slot*>& slots) {
       const Field* src = par ? b : a;
       const Field* dst = par ? a : b;
       GridArgs p1 = make_args(src, dst, &L.f, nullptr, nullptr, h, s->cs_one64, nt[0]);
-      GridArgs p2 = make_args2(src, dst, &L.f, nullptr, h, s->c64_2, nt[1]);
-      GridArgs p3 = make_args3(src, dst, &L.f, nullptr, h, s->c64_3, nt[2]);
+      GridArgs p2 = make_args2(src, dst, &L.f, nullptr, h, c64_2, nt[1]);
+      GridArgs p3 = make_args3(src, dst, &L.f, nullptr, h, c64_3, nt[2]);
       p1.id = p2.id = p3.id = sl->id;
       T[kP64[0][par]][n_in] = p1;
       T[kP64[1][par]][n_in] = p2;
@@ -515,7 +528,6 @@ int queue_cycle64(j3d_server* s, const std::vector<Slot*>& slots) {
       nt[1] += p2.tiles_x * p2.tiles_y * p2.tiles_z;
       nt[2] += p3.tiles_x * p3.tiles_y * p3.tiles_z;
     }
-    pts_in += (long long)L.u.nx() * L.u.ny() * L.u.nz();
     fit3 = fit3 && plane_fits_u32(L.u) && plane_fits_u32(L.w) && plane_fits_u32(L.f);
     ++n_in;
   }
@@ -543,11 +555,11 @@ int queue_cycle64(j3d_server* s, const std::vector<Slot*>& slots) {
                               s->d_conv, s->d_nonfinite, s->st));
   s->passes_in_cycle = 0;
   if (n_in > 0) {
-    const int step = (fit3 && serve_triples64(pts_in)) ? 3 : 2;
+    const int step = (fit3 && serve_triples()) ? 3 : 2;
     auto pass = [&](int len, int par) -> hipError_t {
       const GridArgs* t = D[kP64[len - 1][par]];
-      if (len == 3) return launch_sweep3_batch(J3D_F64, F_WRITE, s->c64_3, t, n_in, nt[2], nullptr, done, s->st);
-      if (len == 2) return launch_sweep2_batch(J3D_F64, F_WRITE, s->c64_2, t, n_in, nt[1], nullptr, done, s->st);
+      if (len == 3) return launch_sweep3_batch(J3D_F64, F_WRITE, c64_3, t, n_in, nt[2], nullptr, done, s->st);
+      if (len == 2) return launch_sweep2_batch(J3D_F64, F_WRITE, c64_2, t, n_in, nt[1], nullptr, done, s->st);
       return launch_pass_batch(J3D_F64, F_WRITE, s->cs_one64, t, n_in, nt[0], nullptr, done, s->st);
     };
     int left = cyc, par = 0;

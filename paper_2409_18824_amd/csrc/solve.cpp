@@ -30,16 +30,12 @@ long long chunk_sweeps(long long points, double bytes_per_point, long long multi
   return n;
 }
 
-// Three-sweep passes pay off once the arrays a pass touches overflow the
-// 256 MB last-level cache: measured on cubes, they save 20-27% per sweep at
-// 384^3 and 512^3, but at 256^3 the cache holds most of the arrays and the
-// three-sweep tile's wider halo cancels the saving (two-sweep passes are
-// as fast or faster there).
-bool three_sweep_passes_pay(double pass_bytes) { return pass_bytes > 512e6; }
-
 // J3D_SOLVE_SWEEPS_PER_PASS=1, 2 or 3 fixes the pass length of both modes
-// (the schedules above, with that step); unset or other values choose it
-// from the grid size.
+// (the schedules below, with that step); unset or other values run
+// three-sweep passes where the cadence of the checks lets them: they take
+// less time per sweep at every size (us per sweep in passes of three against
+// two: FP64 64^3 3.4 / 3.9, 128^3 6.7 / 8.5, 200^3 16 / 20, 512^3 237 / 345;
+// FP32 64^3 2.9 / 3.3, 128^3 5.4 / 6.2, 256^3 18 / 21, 512^3 142 / 200).
 int forced_step() {
   const char* e = std::getenv("J3D_SOLVE_SWEEPS_PER_PASS");
   const int v = e != nullptr ? std::atoi(e) : 0;
@@ -250,28 +246,46 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   const long long S = o.max_sweeps;
   const long long c = o.check_every;
   const long long points = (long long)u.nx() * u.ny() * u.nz();
-  // Passes of `step` sweeps: three on grids whose arrays overflow the
-  // cache, else two when every check falls on an even sweep count, else
-  // one.  A check group of c sweeps opens with one pass of c mod step
-  // sweeps (none when step divides c), which carries the check's residual,
-  // and continues in passes of step sweeps; with three-sweep passes and
-  // c mod 3 = 1 it opens with two two-sweep passes instead, since the
-  // residual of a single sweep leaves many more per-tile partials to
-  // reduce.  A pass ends at the next check and at the end of the range it
-  // belongs to.
+  // Passes of `step` sweeps: three, or two for checks after every second
+  // sweep and one for checks after every sweep.  Three-sweep passes run
+  // straight through the sweeps: the residual of a check is fused into the
+  // pass that forms its iterate, at that stage of the pass, whose input
+  // stays in its array until the check's verdict is known (every later
+  // kernel skips its work once a check has converged), so the checked
+  // iterate can be formed again.  (At the end of a range a shorter pass
+  // stops before a check it would hold past its input.)  With a forced
+  // step of one or two a check group of c sweeps opens with one pass of c
+  // mod step sweeps (none when step divides c), which carries the check's
+  // residual, and continues in passes of step sweeps.
   // (w has u's layout; a three-sweep pass needs planes below 4 GiB)
   const bool fit3 = plane_fits_u32(u) && plane_fits_u32(f);
-  long long step = forced_step() != 0 ? forced_step()
-                   : three_sweep_passes_pay(24.0 * (double)points) ? 3 : ((c % 2) == 0 ? 2 : 1);
+  long long step = forced_step() != 0 ? forced_step() : std::min<long long>(c, 3);
   if (step == 3 && !fit3) step = 2;
   const long long lead = c % step;
-  const bool two_pairs = step == 3 && lead == 1 && c >= 4;
-  auto pass_len = [&](long long sw, long long to) -> int {
-    const long long p = sw % c;
-    const long long len = two_pairs ? ((p == 0 || p == 2) ? 2 : 3) : ((p == 0 && lead != 0) ? lead : step);
-    return (int)std::min(std::min(len, c - p), to - sw);
+  struct Pass {
+    int len;    // sweeps
+    int stage;  // the residual it carries is that of the iterate after this many of them; -1: none
   };
-  const long long group_passes = (lead != 0 ? 1 : 0) + c / step;
+  auto next_pass = [&](long long sw, long long to) -> Pass {
+    if (step != 3) {
+      const long long p = sw % c;
+      const long long len = std::min(p == 0 && lead != 0 ? lead : step, c - p);
+      return Pass{(int)std::min(len, to - sw), p == 0 ? 0 : -1};
+    }
+    int len = (int)std::min<long long>(3, to - sw), stage = -1;
+    for (int o = 0; o < len; ++o) {
+      if ((sw + o) % c != 0) continue;
+      if (stage < 0)
+        stage = o;
+      else
+        len = o;  // the next check opens the next pass
+    }
+    if (stage > 0 && len < 3) return Pass{stage, -1};
+    return Pass{len, stage};
+  };
+  // the schedule repeats after `period` sweeps
+  const long long period = step == 3 && c >= 3 ? std::lcm(c, 3LL) : c;
+  const long long period_passes = step == 3 ? (c >= 3 ? period / 3 : 1) : (lead != 0 ? 1 : 0) + c / step;
 
   // The second ping-pong array has u's layout and starts as a copy of u
   // (which gives it the same halo).
@@ -299,47 +313,50 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   J3D_TRY(norm_f(f, cfg, s, st));
   int* done = &s->ctl->done;
 
-  // which_at[q]: buffer holding the iterate whose residual is check q
+  // which_at[q]: 2 * (sweeps after the input of the pass that carried check
+  // q) + the buffer of that input
   std::vector<unsigned char> which_at((size_t)nchecks, 0);
   // The passes for sweeps [from, to) starting from buffer b (chunk ends are
-  // multiples of c, so chunking never changes the schedule).  Checks take
-  // their index from the device counter, so a chunk is the same kernel
-  // sequence wherever it starts and can be replayed.
+  // multiples of the period, so chunking never changes the schedule).
+  // Checks take their index from the device counter, so a chunk is the same
+  // kernel sequence wherever it starts and can be replayed.
   auto passes = [&](long long from, long long to, int b, hipStream_t q) -> int {
     for (long long sw = from; sw < to;) {
-      const bool check = (sw % c) == 0;
-      const unsigned fl = F_WRITE | (check ? F_RES : 0u);
-      const int len = pass_len(sw, to);
+      const Pass ps = next_pass(sw, to);
+      const unsigned fl =
+          F_WRITE | (ps.stage < 0 ? 0u : ps.stage == 0 ? F_RES : ps.stage == 1 ? F_RES1 : F_RES2);
       int nt;
-      if (len == 3) {
+      if (ps.len == 3) {
         J3D_HIP(launch_sweep3_one(J3D_F64, fl, cfg3, three[b], s->partials, done, q));
         nt = nt3;
-      } else if (len == 2) {
+      } else if (ps.len == 2) {
         J3D_HIP(launch_sweep2_one(J3D_F64, fl, cfg2, two[b], s->partials, done, q));
         nt = nt2;
       } else {
         J3D_HIP(launch_pass_one(J3D_F64, fl, cfg, one[b], s->partials, done, q));
         nt = nt1;
       }
-      sw += len;
-      if (check)
+      sw += ps.len;
+      if (ps.stage >= 0)
         J3D_HIP(launch_reduce_count(s->partials, nt, s->hist, &s->ctl->normf, o.rtol, done, &s->ctl->conv_at,
                                     &s->ctl->nonfinite, &s->ctl->qnext, q));
       b = 1 - b;
     }
     return J3D_OK;
   };
-  // Host mirror of the schedule: the buffer of every check, and at the end.
+  // Host mirror of the schedule: the place of every check, and the buffer at
+  // the end.
   auto track = [&](long long from, long long to, int b) -> int {
     for (long long sw = from; sw < to;) {
-      if (sw % c == 0) which_at[(size_t)(sw / c)] = (unsigned char)b;
-      sw += pass_len(sw, to);
+      const Pass ps = next_pass(sw, to);
+      if (ps.stage >= 0) which_at[(size_t)((sw + ps.stage) / c)] = (unsigned char)(2 * ps.stage + b);
+      sw += ps.len;
       b = 1 - b;
     }
     return b;
   };
-  const long long unit = group_passes % 2 == 0 ? c : 2 * c;  // an even number of passes
-  const long long chunk = chunk_sweeps(points, 24.0 * group_passes / c, unit);
+  const long long unit = period_passes % 2 == 0 ? period : 2 * period;  // an even number of passes
+  const long long chunk = chunk_sweeps(points, 24.0 * period_passes / period, unit);
   long long sw = 0;
   int cur = 0;
   int slot = 0;
@@ -400,7 +417,13 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   if (ctl.done) {
     sweeps = ctl.conv_at * c;
     nh = ctl.conv_at + 1;
-    at = which_at[(size_t)ctl.conv_at];
+    at = which_at[(size_t)ctl.conv_at] & 1;
+    // the checked iterate was formed inside a pass: form it again from the
+    // pass's input, into the other array
+    const int again = which_at[(size_t)ctl.conv_at] >> 1;
+    if (again == 1) J3D_HIP(launch_pass_one(J3D_F64, F_WRITE, cfg, one[at], nullptr, nullptr, st));
+    if (again == 2) J3D_HIP(launch_sweep2_one(J3D_F64, F_WRITE, cfg2, two[at], nullptr, nullptr, st));
+    if (again > 0) at = 1 - at;
   } else {
     sweeps = S;
     nh = S / c + 1;
@@ -460,12 +483,11 @@ int solve_mixed(const Field& u, const Field& f, double h, const j3d_solve_opts& 
   J3D_HIP(hipMemsetAsync(mem, 0, 3 * b1, st));  // zero halos of the correction
 
   // A cycle of m correction sweeps e_1 = J(0), e_{p+1} = J(e_p), u += e_m
-  // runs as passes of `step` sweeps (three on grids whose arrays overflow
-  // the cache, else two): the first pass starts from zero without reading
-  // it (m mod step sweeps, step when step divides m), the middle passes
+  // runs as passes of `step` sweeps: the first pass starts from zero without
+  // reading it (m mod step sweeps, step when step divides m), the middle passes
   // ping-pong between e0 and e1, and the last pass adds its result to u.
   const long long points = (long long)u.nx() * u.ny() * u.nz();
-  int step = forced_step() != 0 ? forced_step() : three_sweep_passes_pay(12.0 * (double)points) ? 3 : 2;
+  int step = forced_step() != 0 ? forced_step() : 3;
   if (step == 3 && !(plane_fits_u32(u) && plane_fits_u32(r32))) step = 2;
   const TileCfg cs2 = default_cfg2(J3D_F32, u.nx(), u.ny(), u.nz());
   const TileCfg cs3 = default_cfg3(J3D_F32, u.nx(), u.ny(), u.nz());

@@ -512,3 +512,15 @@ def test_serve_create_validation_before_device_work():
         assert lib.poisson_serve_create(ctypes.byref(opts(**bad)), ctypes.byref(h)) == j3d.EINVAL, bad
     assert "precision" in (lib.poisson_serve_create(ctypes.byref(opts(precision=7)), ctypes.byref(h)) and
                            j3d.last_error())
+
+
+@pytest.mark.parametrize("kind", [j3d.KIND_F64X2, j3d.KIND_F32X2, j3d.KIND_F64X3, j3d.KIND_F32X3])
+def test_default_multi_sweep_shapes_are_supported(kind):
+    """The shape picked for any size is one the pass has (the pinning call
+    accepts it), on flat, pencil-shaped and cubic grids of every size range."""
+    for nx, ny, nz in [(1, 1, 1), (16, 16, 16), (4096, 1, 1), (1, 4096, 1), (1, 1, 4096), (3, 70, 900), (40, 40, 40),
+                       (200, 1, 3000), (255, 256, 256), (256, 256, 256), (400, 400, 400), (401, 400, 400),
+                       (1 << 14, 1 << 10, 1), (1, 1 << 12, 4095)]:
+        t = j3d.j3d_tune_query_single(kind, nx, ny, nz)
+        j3d.j3d_tune_set_single(kind, nx, ny, nz, t)
+        assert j3d.j3d_tune_query_single(kind, nx, ny, nz) == t

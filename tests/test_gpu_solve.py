@@ -250,3 +250,26 @@ def test_large_grids_choose_three_sweep_passes(mode, shape, every, monkeypatch):
     assert res.sweeps == ro.sweeps and len(res.history) == len(ro.history)
     assert all(rel(a, b) <= RESID_RTOL for a, b in zip(res.history, ro.history))
     assert np.array_equal(du.to_numpy(), uo)
+
+
+@pytest.mark.parametrize("every", [3, 4, 5, 7])
+@pytest.mark.parametrize("rtol", [0.9, 0.5, 0.2, 3e-2, 3e-3])
+def test_early_exit_inside_three_sweep_passes(every, rtol):
+    """Passes run straight through the checks: whichever stage of a pass forms
+    the converged iterate (every position of a check in the passes of three
+    occurs), and inside replayed chunks, the solve returns the oracle's
+    iterate and history."""
+    n = (23, 17, 20)
+    say("early exit inside passes", every, rtol)
+    h = 1.0 / 24
+    u0 = synth.uniform_field(*n, 12, 1, 0, 1)
+    f = synth.manufactured_f(*n, h)
+    du, df = j3d.FArray.from_numpy(u0), j3d.FArray.from_numpy(f)
+    # a first guess far off, so that the relative residual falls from about 10
+    res = j3d.poisson_solve(du, df, h, rtol=rtol, max_sweeps=20000, check_every=every)
+    uo, ro = oracle.solve_plain(u0, f, h, rtol=rtol, check_every=every, max_sweeps=20000)
+    assert res.converged == ro.converged and res.sweeps == ro.sweeps
+    assert len(res.history) == len(ro.history)
+    assert all(rel(a, b) <= RESID_RTOL for a, b in zip(res.history, ro.history))
+    assert rel(res.resid, ro.resid) <= RESID_RTOL
+    assert np.array_equal(du.to_numpy(), uo)

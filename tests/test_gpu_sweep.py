@@ -374,3 +374,43 @@ def test_bandwidth_probe_sane():
     say("two reads + one write GB/s", g3)
     assert torch.equal(b, torch.full_like(b, 3.0))
     assert 500.0 < g3 < 8000.0 * 1.05
+
+
+@pytest.mark.parametrize("shape", [(16, 16, 16), (15, 17, 16), (33, 65, 17), (64, 64, 64), (100, 250, 79), (300, 40, 146),
+                                   (128, 128, 129), (181, 143, 160), (257, 255, 256)])
+def test_default_shapes_of_the_size_ranges(shape):
+    """One, two and three sweeps with the shapes the library picks by size
+    (both sides of the lines between the ranges), storing plainly (passes of
+    40 to 256 MB) and nontemporally: oracle bits, the residual at each stage,
+    halo and input untouched; FP32 two and three sweeps too."""
+    nx, ny, nz = shape
+    say("default shapes", shape)
+    u, f, h = make_inputs(nx, ny, nz, seed=13)
+    its = [u]
+    for _ in range(3):
+        its.append(oracle.sweep(its[-1], f, h))
+    norms = [oracle.residual_l2(it, f, h) for it in its[:3]]
+    du, df = j3d.FArray.from_numpy(u), j3d.FArray.from_numpy(f)
+    r = torch.zeros(5, dtype=torch.float64, device="cuda")
+    calls = [(1, j3d.jacobi3d_sweep, {}), (2, j3d.jacobi3d_sweep2, {}), (3, j3d.jacobi3d_sweep3, {}),
+             (3, j3d.jacobi3d_sweep3, dict(resid_after=1)), (3, j3d.jacobi3d_sweep3, dict(resid_after=2))]
+    for q, (n, fn, kw) in enumerate(calls):
+        dv = j3d.FArray.from_numpy(u)
+        dv.view()[1:-1, 1:-1, 1:-1] = -7.0
+        fn(du, dv, df, h, resid_out=r[q:q + 1], **kw)
+        torch.cuda.synchronize()
+        assert np.array_equal(dv.to_numpy(), its[n]), (n, kw)
+        assert rel(float(r[q].item()), norms[kw.get("resid_after", 0)]) <= RESID_RTOL, (n, kw)
+    assert np.array_equal(du.to_numpy(), u)
+    u32, f32 = u.astype(np.float32), f.astype(np.float32)
+    h2 = np.float32(h * h)
+    a, b = j3d.FArray.from_numpy(u32, dtype=j3d.F32), j3d.FArray.from_numpy(f32, dtype=j3d.F32)
+    it = [u32]
+    for _ in range(3):
+        it.append(oracle.sweep_f32(it[-1], f32, h2))
+    for n, fn in ((1, j3d.jacobi3d_sweep), (2, j3d.jacobi3d_sweep2), (3, j3d.jacobi3d_sweep3)):
+        o = j3d.FArray.from_numpy(u32, dtype=j3d.F32)
+        o.view()[1:-1, 1:-1, 1:-1] = -7.0
+        fn(a, o, b, h)
+        torch.cuda.synchronize()
+        assert np.array_equal(o.to_numpy(), it[n]), n
