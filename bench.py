@@ -650,8 +650,8 @@ def advect_source_hash() -> str:
 
 
 def advect_tile() -> str:
-    return "%s/%s/%s" % (os.environ.get("J3D_ADVECT_TILE", "default"), os.environ.get("J3D_TRACER2_TILE", "default"),
-                         os.environ.get("J3D_TRACER_STEPS_PER_PASS", "default"))
+    return "/".join(os.environ.get(k, "default") for k in ("J3D_ADVECT_TILE", "J3D_TRACER2_TILE", "J3D_TRACER3_TILE",
+                                                           "J3D_TRACER_STEPS_PER_PASS"))
 
 
 def advect_traffic(name: str):
@@ -771,10 +771,12 @@ def run_tra_adv(args):
     times = _event_times(call, args.steps)
     med = float(np.median(times))
     pts = nx * ny * nz
-    # the library's schedule: two steps per launch (one pass over memory),
-    # unless J3D_TRACER_STEPS_PER_PASS=1; S = 20 needs no single-step launch
-    per_launch = 1 if os.environ.get("J3D_TRACER_STEPS_PER_PASS") == "1" else 2
-    launches = S // per_launch
+    # the library's schedule: three steps per launch (one pass over memory)
+    # unless J3D_TRACER_STEPS_PER_PASS says 1 or 2, what is left of S in
+    # single-step launches (two for S = 20)
+    env_steps = os.environ.get("J3D_TRACER_STEPS_PER_PASS")
+    per_launch = int(env_steps) if env_steps in ("1", "2") else 3
+    launches = S // per_launch + S % per_launch
     alg = 48 * pts  # per launch: read t, u, v, w, r and write t once per point
     out = _base(args, "point updates per second (tracer advection, 6 fields, %dx%dx%d, %d steps)" % (nx, ny, nz, S),
                 round(pts * S / med / 1e9, 2), "GLUP/s", round(med * 1e3, 3), "f64",

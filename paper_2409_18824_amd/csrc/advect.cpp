@@ -1,6 +1,7 @@
 // pw_advection / tracer_advection: the multi-field stencils standing in for
 // the paper's pw-advection and tra-adv benchmarks (Sec. "Flang performance
 // comparison": field counts and grid sizes only).
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -12,14 +13,47 @@ using namespace j3d;
 
 namespace {
 
-// Tile shapes measured fastest on the paper's grids, nontemporal stores
-// throughout: for the momentum advection (2048 x 1024 x 1024) 4 rows per
-// thread, 64 z-planes per wavefront, loads one plane ahead (19.5 ms per call
-// against 20.2 with 8 rows, 128 planes and no prefetch); for the tracer
-// (1024 x 512 x 512) 8 rows, 64 planes.
-// J3D_ADVECT_TILE="ry,planes,nt[,pf]" overrides both (shape sweeps).
-AdvectCfg advect_cfg(bool tracer) {
-  AdvectCfg c = tracer ? AdvectCfg{8, 64, 1, 0} : AdvectCfg{4, 64, 1, 1};
+// A workgroup shape and what a step of its march costs (us) with j workgroups
+// on a CU: h + g * j, at most `per_cu` of them.  Fitted to timed passes over
+// nine grids from 64^3 to 1024 x 512 x 512.
+struct MarchShape {
+  int ry, cols, rows;  // rows per thread; columns and rows a workgroup outputs
+  int per_cu;
+  double h, g;
+  double extra;  // steps of a march beyond its planes
+};
+const MarchShape kPwShapes[] = {{2, 64, 8, 3, 0.2, 1.0, 2}, {4, 64, 16, 2, 0.0, 1.82, 2}};
+const MarchShape kTracer3Shapes[] = {{3, 58, 8, 2, 0.32, 0.95, 5}, {4, 58, 28, 1, 2.8, 0.2, 5}};
+
+// The shape and number of planes with the least estimated time: few planes
+// where the grid would leave CUs idle otherwise, many where the planes that
+// each chunk reads beyond its own cost more.
+template <size_t N>
+AdvectCfg march_shape(const MarchShape (&shapes)[N], const AdvArgs& a) {
+  AdvectCfg best{};
+  double least = 0.0;
+  for (const MarchShape& s : shapes) {
+    const long long tiles =
+        ((a.nx + s.cols - 1LL) / s.cols) * ((a.ny + s.rows - 1LL) / s.rows);
+    for (int planes = 4; planes <= 128; ++planes) {
+      const int chunks = (a.nz + planes - 1) / planes;
+      const long long per_cu = (tiles * chunks + 255) / 256;
+      const long long full = per_cu / s.per_cu, rest = per_cu % s.per_cu;
+      const double t = (std::min(planes, a.nz) + s.extra) *
+                       (full * (s.h + s.g * s.per_cu) + (rest ? s.h + s.g * rest : 0.0));
+      if (best.ry == 0 || t < least) {
+        least = t;
+        best.ry = s.ry;
+        best.planes = planes;
+      }
+    }
+  }
+  return best;
+}
+
+// J3D_ADVECT_TILE="ry,planes,nt[,pf]" overrides the momentum advection's and
+// the single tracer step's tile shape (shape sweeps).
+AdvectCfg advect_cfg_from_env(AdvectCfg c) {
   if (const char* e = std::getenv("J3D_ADVECT_TILE")) {
     AdvectCfg t{0, 0, 0, 0};
     const int n = std::sscanf(e, "%d,%d,%d,%d", &t.ry, &t.planes, &t.nt, &t.pf);
@@ -28,14 +62,37 @@ AdvectCfg advect_cfg(bool tracer) {
   return c;
 }
 
+// Momentum advection: loads one plane ahead and nontemporal stores throughout
+// (within 3 % of plain ones at every size).  Fixed tiles of 4 rows and 64
+// planes took 106 us at 64^3 (now 7.2), 109 at 128^3 (22), 247 at 500 x 300 x
+// 100 (155), the same at 256^3 and above.
+AdvectCfg pw_cfg(const AdvArgs& a) {
+  AdvectCfg c = march_shape(kPwShapes, a);
+  c.nt = c.pf = 1;
+  return advect_cfg_from_env(c);
+}
+
+// Single tracer step: rows and planes by the number of points (us per step
+// with 8 rows and 64 planes / these: 64^3 188 / 6.0, 128^3 189 / 17.0, 256^3
+// 228 / 159, 400^3 782 / 661, 1024 x 512 x 512 2449 / 2449).
+AdvectCfg tracer_cfg(const AdvArgs& a) {
+  const double pts = (double)a.nx * a.ny * a.nz;
+  AdvectCfg c = pts < 1e6   ? AdvectCfg{2, 4, 1}
+                : pts < 5e6 ? AdvectCfg{2, 8, 1}
+                : pts < 3e7 ? AdvectCfg{4, 4, 1}
+                : pts < 1e8 ? AdvectCfg{4, 20, 1}
+                            : AdvectCfg{8, 64, 1};
+  return advect_cfg_from_env(c);
+}
+
 // Every plane (interior and halo) of the field under 2^31 bytes.
 bool plane_below_2gib(const Field& a) {
   return ((long long)(a.ey - 1) * a.sy + a.ex) * (long long)a.esize < (1LL << 31);
 }
 
-// Two-step tracer pass: 6 rows per thread, 64 planes, nontemporal stores
+// Two-step tracer pass (planes of 2^31 bytes and more): 6 rows per thread, 64 planes, nontemporal stores
 // (fastest at 1024 x 512 x 512).  J3D_TRACER2_TILE="ry,planes,nt" overrides
-// it; J3D_TRACER_STEPS_PER_PASS=1 runs every step as its own pass.
+// it.
 AdvectCfg tracer2_cfg() {
   AdvectCfg c{6, 64, 1};
   if (const char* e = std::getenv("J3D_TRACER2_TILE")) {
@@ -45,9 +102,28 @@ AdvectCfg tracer2_cfg() {
   return c;
 }
 
-bool tracer_two_steps_per_pass() {
+// Three-step tracer pass: by estimate, but 64 planes from 2^24 points on
+// (fastest at 256^3, 400^3 and 1024 x 512 x 512 by 1 to 6 %); plain stores
+// (the next pass reads the iterate) while the fields stay below 4 GB: 128^3
+// 11.9 against 12.7 us per step, 400^3 263 against 266, 1024 x 512 x 512 1033
+// against 1008.  J3D_TRACER3_TILE="ry,planes,nt" overrides it.
+AdvectCfg tracer3_cfg(const AdvArgs& a) {
+  const double pts = (double)a.nx * a.ny * a.nz;
+  AdvectCfg c = pts < (double)(1 << 24) ? march_shape(kTracer3Shapes, a) : AdvectCfg{4, 64, 0};
+  c.nt = pts * 48.0 >= 4e9;
+  if (const char* e = std::getenv("J3D_TRACER3_TILE")) {
+    AdvectCfg t{0, 0, 0};
+    if (std::sscanf(e, "%d,%d,%d", &t.ry, &t.planes, &t.nt) == 3 && tracer3_cfg_supported(t)) c = t;
+  }
+  return c;
+}
+
+// Steps per pass of tracer_advection, 1, 2 or 3 (J3D_TRACER_STEPS_PER_PASS).
+int tracer_steps_per_pass(const AdvArgs& a) {
   const char* e = std::getenv("J3D_TRACER_STEPS_PER_PASS");
-  return !(e != nullptr && std::atoi(e) == 1);
+  const int n = e != nullptr ? std::atoi(e) : 0;
+  if (n == 1 || n == 2) return n;
+  return a.buffer_ok ? 3 : 2;
 }
 
 int check_spacing(double d, const char* name) {
@@ -100,7 +176,7 @@ extern "C" int pw_advection(const j3d_array* u, const j3d_array* v, const j3d_ar
   a.buffer_ok = 1;
   for (int q = 0; q < 6; ++q)
     if (!plane_below_2gib(f[q])) a.buffer_ok = 0;
-  J3D_HIP(launch_pw_advect(a, advect_cfg(false), static_cast<hipStream_t>(stream)));
+  J3D_HIP(launch_pw_advect(a, pw_cfg(a), static_cast<hipStream_t>(stream)));
   return J3D_OK;
 }
 
@@ -123,29 +199,35 @@ extern "C" int tracer_advection(j3d_array* t_a, j3d_array* t_b, const j3d_array*
   a.nz = f[0].nz();
   a.siy = a.soy = (int)f[0].sy;
   a.siz = a.soz = f[0].sz;
-  const AdvectCfg c1 = advect_cfg(true);
+  const AdvectCfg c1 = tracer_cfg(a);
   const AdvectCfg c2 = tracer2_cfg();
+  const AdvectCfg c3 = tracer3_cfg(a);
   hipStream_t st = static_cast<hipStream_t>(stream);
   double* ta = reinterpret_cast<double*>(f[0].base);
   double* tb = reinterpret_cast<double*>(f[1].base);
-  // n2 launches of two steps, then n1 of one; every launch swaps the arrays,
-  // so the number of launches keeps the parity of niter (one two-step launch
-  // is split in two when it would not) and the result is in t_a exactly when
-  // niter is even.
-  int64_t n2 = tracer_two_steps_per_pass() ? niter / 2 : 0;
-  int64_t n1 = niter - 2 * n2;
-  if (((n2 + n1) & 1) != (niter & 1)) {
-    n2 -= 1;
-    n1 += 2;
+  a.buffer_ok = 1;
+  for (int q = 0; q < 6; ++q)
+    if (!plane_below_2gib(f[q])) a.buffer_ok = 0;
+  // Launches of `per` steps, then single ones.  Every launch swaps the
+  // arrays, so the number of launches keeps the parity of niter (a pass of
+  // two steps is split in two when it would not) and the result is in t_a
+  // exactly when niter is even.
+  const int per = tracer_steps_per_pass(a);
+  int64_t nl = niter / per, n1 = niter % per;
+  if (((nl + n1) & 1) != (niter & 1)) {
+    nl -= 1;
+    n1 += per;
   }
   bool from_a = true;
-  for (int64_t q = 0; q < n2 + n1; ++q) {
+  for (int64_t q = 0; q < nl + n1; ++q) {
     a.t = from_a ? ta : tb;
     a.out[0] = from_a ? tb : ta;
-    if (q < n2)
+    if (q >= nl || per == 1)
+      J3D_HIP(launch_tracer_advect(a, c1, st));
+    else if (per == 2)
       J3D_HIP(launch_tracer2_advect(a, c2, st));
     else
-      J3D_HIP(launch_tracer_advect(a, c1, st));
+      J3D_HIP(launch_tracer3_advect(a, c3, st));
     from_a = !from_a;
   }
   return J3D_OK;

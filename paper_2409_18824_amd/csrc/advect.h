@@ -41,5 +41,9 @@ hipError_t launch_tracer_advect(const AdvArgs& a, const AdvectCfg& c, hipStream_
 // later); rows per thread 2, 4 or 6.
 bool tracer2_cfg_supported(const AdvectCfg& c);
 hipError_t launch_tracer2_advect(const AdvArgs& a, const AdvectCfg& c, hipStream_t st);
+// Three tracer steps per launch; 3 rows per thread in workgroups of 4
+// wavefronts or 4 rows in workgroups of 8; needs AdvArgs::buffer_ok.
+bool tracer3_cfg_supported(const AdvectCfg& c);
+hipError_t launch_tracer3_advect(const AdvArgs& a, const AdvectCfg& c, hipStream_t st);
 
 }  // namespace j3d

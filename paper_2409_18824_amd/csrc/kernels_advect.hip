@@ -83,16 +83,34 @@ __device__ __forceinline__ TileMap tile_of(const AdvArgs& a, int ry) {
   return m;
 }
 
+// The value of lane l-1 / l+1; zero in lane 0 / lane 63, whose neighbour the
+// callers take from elsewhere or do not use (nothing to keep there, so the
+// shift needs no copy of its operand first).
+__device__ __forceinline__ double left_lane(double v) {
+  const sweep_detail::dpp_i2 a = __builtin_bit_cast(sweep_detail::dpp_i2, v);
+  sweep_detail::dpp_i2 r;
+  r.x = __builtin_amdgcn_mov_dpp(a.x, 0x138, 0xF, 0xF, true);
+  r.y = __builtin_amdgcn_mov_dpp(a.y, 0x138, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, r);
+}
+__device__ __forceinline__ double right_lane(double v) {
+  const sweep_detail::dpp_i2 a = __builtin_bit_cast(sweep_detail::dpp_i2, v);
+  sweep_detail::dpp_i2 r;
+  r.x = __builtin_amdgcn_mov_dpp(a.x, 0x130, 0xF, 0xF, true);
+  r.y = __builtin_amdgcn_mov_dpp(a.y, 0x130, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, r);
+}
+
 // Left / right x-neighbour of value v of row r, whose halo columns are in
 // the gathered vector g (lane r: left, lane 32+r: right).
 __device__ __forceinline__ double nb_left(double v, double g, int r, int lane) {
   const double h = lane_value(g, r);
-  const double s = from_left(v);
+  const double s = left_lane(v);
   return lane == 0 ? h : s;
 }
 __device__ __forceinline__ double nb_right(double v, double g, int r, int lane) {
   const double h = lane_value(g, 32 + r);
-  const double s = from_right(v);
+  const double s = right_lane(v);
   return lane == WAVE - 1 ? h : s;
 }
 
@@ -296,10 +314,19 @@ __global__ void __launch_bounds__(WAVE * kWaves) k_pw_advect_pf(AdvArgs a) {
   flush(m.k1 - 1, true);
 }
 
-__device__ __forceinline__ double upwind(double q, double below, double above) {
-  const double qp = q > 0.0 ? q : 0.0;
-  const double qm = q < 0.0 ? q : 0.0;
+// q > 0 ? q : 0 and q < 0 ? q : 0 are the maximum and the minimum of
+// q + 0.0 with zero, bit for bit: the addition makes -0 +0 and quiets a NaN,
+// for which both then return the zero.  (v_max_f64 and v_min_f64 by name: the
+// compiler's forms quiet their operand once more.)
+__device__ __forceinline__ double plain_zero(double q) { return q + 0.0; }
+__device__ __forceinline__ double upwind_plain(double p, double below, double above) {
+  double qp, qm;
+  asm("v_max_f64 %0, %1, 0" : "=v"(qp) : "v"(p));
+  asm("v_min_f64 %0, %1, 0" : "=v"(qm) : "v"(p));
   return qp * below + qm * above;
+}
+__device__ __forceinline__ double upwind(double q, double below, double above) {
+  return upwind_plain(plain_zero(q), below, above);
 }
 
 // in[0..3] = u, v, w, r; t = input iterate; out[0] = output iterate.
@@ -522,6 +549,190 @@ __global__ void __launch_bounds__(WAVE * kWaves) k_tracer2_advect(AdvArgs a) {
   }
 }
 
+// Three tracer steps in one pass: t3 = S(S(S(t0))), u, v, w, r read once for
+// all of them.  Lane l is column x0 - 3 + l (tiles 58 wide); a workgroup of
+// WV wavefronts of RY rows each outputs all but its outer two rows.  Step k
+// of the march forms t1 at plane k, t2 at plane k-1 and t3 at plane k-2.
+// Every flux is formed once: the west flux is the neighbouring lane's east
+// flux, the south flux the row below's north flux, the bottom flux the
+// previous plane's top flux (same operands, same bits).  Three planes of the
+// fields stay in registers and a fourth is in flight; the t1 and t2 rows of
+// the neighbouring wavefronts pass through LDS in two slots, one barrier per
+// plane.  Needs AdvArgs::buffer_ok.
+//
+// Bound by memory: 1024 x 512 x 512 moves 15.5 GB per pass (12.9 without the
+// overlap of the tiles) at 5.2 TB/s, and takes 2.95 instead of 3.03 ms with
+// the arithmetic left out; 1.00 ms per step against 1.42 with two steps per
+// pass and 2.45 with one.  4 rows in 8 wavefronts fill a CU's registers (250
+// each) and have the least overlap (a fourth step would not fit); workgroups
+// of 3 rows in 4 wavefronts are for grids too small to fill the chip with
+// those (64^3: 4.4 us per step, 8.3 with 4 x 8).  Keeping the older planes in
+// LDS instead of registers took 8 % longer.
+constexpr int kOut3 = WAVE - 6;  // outputs per wavefront along x
+
+template <int RY, int WV, bool NT>
+__global__ void __launch_bounds__(WAVE * WV, 8 / WV) k_tracer3_advect(AdvArgs a) {
+  using sweep_detail::bload;
+  using sweep_detail::bstore;
+  using sweep_detail::kDropOffset;
+  using sweep_detail::plane_rsrc_n;
+  constexpr int TR = WV * RY;  // workgroup rows
+  constexpr int H = TR - 4;    // output rows
+  __shared__ double edge[2][2][WV][2][WAVE];    // plane slot, t1/t2, wavefront, first/last row
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int wy = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  const int tx = b % a.tiles_x;
+  const int rest = b / a.tiles_x;
+  const int ty = rest % a.tiles_y;
+  const int kc = rest / a.tiles_y;
+  const int x = tx * kOut3 - 2 + lane;  // x0 - 3 + lane
+  const int xc = min(max(x, 0), a.nx + 1);
+  const bool x_in = x >= 1 && x <= a.nx;
+  const bool lane_out = lane >= 3 && lane < kOut3 + 3 && x_in;
+  const int y0 = ty * H + wy * RY - 1;  // row of this wavefront's first own row
+  const int k0 = 1 + kc * a.planes;
+  const int k1 = min(k0 + a.planes, a.nz + 1);
+  uint32_t roff[RY + 2], oo[RY];  // byte offsets of rows y0-1 .. y0+RY (clamped); of the outputs
+  bool in[RY];
+#pragma unroll
+  for (int i = 0; i < RY + 2; ++i) roff[i] = (uint32_t)(xc + a.siy * min(max(y0 - 1 + i, 0), a.ny + 1)) * 8u;
+#pragma unroll
+  for (int r = 0; r < RY; ++r) {
+    const int y = y0 + r, br = wy * RY + r;
+    in[r] = x_in && y >= 1 && y <= a.ny;
+    oo[r] = lane_out && br >= 2 && br < TR - 2 && y <= a.ny ? (uint32_t)(x + a.soy * y) * 8u : kDropOffset;
+  }
+  const uint32_t rin = ((uint32_t)(a.nx + 1) + (uint32_t)a.siy * (uint32_t)(a.ny + 1) + 1u) * 8u;
+  const uint32_t rout = ((uint32_t)(a.nx + 1) + (uint32_t)a.soy * (uint32_t)(a.ny + 1) + 1u) * 8u;
+  const uint64_t zin = (uint64_t)a.siz * 8u, zout = (uint64_t)a.soz * 8u;
+  auto rsrc = [&](const double* p, int k) { return plane_rsrc_n(p, zin, min(max(k, 0), a.nz + 1), rin); };
+  struct Fields {
+    double u[RY], w[RY], r[RY], v[RY + 1];  // v[i]: row y0 - 1 + i
+  };
+  Fields O, P, C, N;                          // planes k-2, k-1, k, k+1 (in flight)
+  double A0[RY + 2], A1[RY + 2], TN[RY + 2];  // t0 at planes k, k+1, k+2 (in flight)
+  double B0[RY], B1[RY];                      // t1 at planes k-1, k
+  double D0[RY], D1[RY];                      // t2 at planes k-2, k-1
+  double F1[RY], F2[RY], F3[RY];        // bottom fluxes of the three stages' planes
+  auto load_t = [&](double (&t)[RY + 2], int k) {
+    const auto rs = rsrc(a.t, k);
+#pragma unroll
+    for (int i = 0; i < RY + 2; ++i) t[i] = bload<double>(rs, roff[i]);
+  };
+  auto load_f = [&](Fields& f, int k) {
+    const auto ru = rsrc(a.in[0], k), rv = rsrc(a.in[1], k), rw = rsrc(a.in[2], k), rr = rsrc(a.in[3], k);
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      f.u[r] = bload<double>(ru, roff[r + 1]);
+      f.w[r] = bload<double>(rw, roff[r + 1]);
+      f.r[r] = bload<double>(rr, roff[r + 1]);
+    }
+#pragma unroll
+    for (int i = 0; i < RY + 1; ++i) f.v[i] = bload<double>(rv, roff[i]);
+  };
+  {
+    double w[RY];
+    const auto rw = rsrc(a.in[2], k0 - 3);
+    load_t(A1, k0 - 3);
+#pragma unroll
+    for (int r = 0; r < RY; ++r) w[r] = bload<double>(rw, roff[r + 1]);
+    load_t(A0, k0 - 2);
+    load_t(TN, k0 - 1);
+    load_f(N, k0 - 2);
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      F1[r] = upwind(w[r], A1[r + 1], A0[r + 1]);
+      F2[r] = F3[r] = B0[r] = D0[r] = 0.0;
+      C.u[r] = C.w[r] = C.r[r] = 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < RY + 1; ++i) C.v[i] = 0.0;
+    P = C;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) edge[(k0 - 3) & 1][i][wy][e][lane] = 0.0;
+  }
+  // One step at one plane: the next iterate from t (own rows; ts, tn: the
+  // rows below and above them), up (the plane above) and the fields; bot
+  // holds the bottom fluxes and takes the top ones, the next plane's bottom.
+  // Halo cells keep their value.
+  auto stage = [&](const double* t, double ts, double tn, const double* up, const Fields& f, double (&bot)[RY],
+                   double (&out)[RY], bool k_in) {
+    double fs = upwind_plain(f.v[0], ts, t[0]);
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      const double tc = t[r];
+      const double fe = upwind_plain(f.u[r], tc, right_lane(tc));
+      const double fw = left_lane(fe);
+      const double fn = upwind_plain(f.v[r + 1], tc, r == RY - 1 ? tn : t[r + 1]);
+      const double ft = upwind_plain(f.w[r], tc, up[r]);
+      const double div = ((fe - fw) + (fn - fs)) + (ft - bot[r]);
+      const double v = tc - f.r[r] * div;
+      out[r] = in[r] && k_in ? v : tc;
+      fs = fn;
+      bot[r] = ft;
+    }
+  };
+  const int wb = max(wy - 1, 0), wa = min(wy + 1, WV - 1);  // (the ring rows' values go unused)
+  for (int k = k0 - 2; k < k1 + 2; ++k) {
+    O = P;
+    P = C;
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      C.u[r] = plain_zero(N.u[r]);
+      C.w[r] = plain_zero(N.w[r]);
+      C.r[r] = N.r[r];
+    }
+#pragma unroll
+    for (int i = 0; i < RY + 1; ++i) C.v[i] = plain_zero(N.v[i]);
+#pragma unroll
+    for (int i = 0; i < RY + 2; ++i) A1[i] = TN[i];
+    load_t(TN, k + 2);
+    load_f(N, k + 1);
+    __syncthreads();
+    const int so = (k - 1) & 1;
+    stage(A0 + 1, A0[0], A0[RY + 1], A1 + 1, C, F1, B1, k >= 1 && k <= a.nz);
+    __builtin_amdgcn_sched_barrier(0);
+    stage(B0, edge[so][0][wb][1][lane], edge[so][0][wa][0][lane], B1, P, F2, D1, k >= 2 && k <= a.nz + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    double t3[RY];
+    stage(D0, edge[so][1][wb][1][lane], edge[so][1][wa][0][lane], D1, O, F3, t3, true);
+    const auto ro = plane_rsrc_n(a.out[0], zout, max(k - 2, 0), rout);
+#pragma unroll
+    for (int r = 0; r < RY; ++r) bstore<double, NT>(t3[r], ro, k - 2 >= k0 ? oo[r] : kDropOffset);
+    edge[k & 1][0][wy][0][lane] = B1[0];
+    edge[k & 1][0][wy][1][lane] = B1[RY - 1];
+    edge[k & 1][1][wy][0][lane] = D1[0];
+    edge[k & 1][1][wy][1][lane] = D1[RY - 1];
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      B0[r] = B1[r];
+      D0[r] = D1[r];
+    }
+#pragma unroll
+    for (int i = 0; i < RY + 2; ++i) A0[i] = A1[i];
+    // (keeps the copies of the arriving planes, and the wait that comes with
+    // them, behind everything else of the step)
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+template <int RY, int WV, bool NT>
+hipError_t go3(AdvArgs a, hipStream_t st) {
+  constexpr int h = WV * RY - 4;  // output rows per workgroup
+  a.tiles_x = (a.nx + kOut3 - 1) / kOut3;
+  a.tiles_y = (a.ny + h - 1) / h;
+  a.yblocks = a.tiles_y;
+  const int zchunks = (a.nz + a.planes - 1) / a.planes;
+  const long long blocks = (long long)a.tiles_x * a.tiles_y * zchunks;
+  if (blocks <= 0) return hipSuccess;
+  if (blocks >= (1LL << 31)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_tracer3_advect<RY, WV, NT>), dim3((unsigned)blocks), dim3(WAVE * WV), 0, st, a);
+  return hipGetLastError();
+}
+
 template <typename Kernel>
 hipError_t go2(Kernel kern, AdvArgs a, int ry, hipStream_t st) {
   const int h = kWaves * ry - 2;  // output rows per workgroup
@@ -609,6 +820,18 @@ hipError_t launch_tracer2_advect(const AdvArgs& a, const AdvectCfg& c, hipStream
     case 12: return go2(k_tracer2_advect<6, false>, g, 6, st);
     default: return go2(k_tracer2_advect<6, true>, g, 6, st);
   }
+}
+
+bool tracer3_cfg_supported(const AdvectCfg& c) {
+  return (c.ry == 3 || c.ry == 4) && c.planes >= 1 && (c.nt == 0 || c.nt == 1);
+}
+
+hipError_t launch_tracer3_advect(const AdvArgs& a, const AdvectCfg& c, hipStream_t st) {
+  if (!tracer3_cfg_supported(c) || !a.buffer_ok) return hipErrorInvalidValue;
+  AdvArgs g = a;
+  g.planes = c.planes;
+  if (c.ry == 3) return c.nt ? go3<3, 4, true>(g, st) : go3<3, 4, false>(g, st);
+  return c.nt ? go3<4, 8, true>(g, st) : go3<4, 8, false>(g, st);
 }
 
 }  // namespace j3d

@@ -209,3 +209,52 @@ def test_non_finite_inputs_follow_the_oracle(monkeypatch):
         j3d.tracer_advection(da, db, *[j3d.FArray.from_numpy(a) for a in q + [r]], 4)
         torch.cuda.synchronize()
         assert np.array_equal(da.to_numpy(), want, equal_nan=True), steps
+
+
+# three-step tracer passes: x tiles 58 wide; 3 rows in 4 wavefronts (8 output
+# rows) or 4 rows in 8 (28); None is the library's own choice
+@pytest.mark.parametrize("shape", [(1, 1, 1), (57, 8, 3), (58, 9, 4), (59, 28, 5), (117, 29, 13), (64, 57, 2),
+                                   (174, 31, 9), (20, 20, 140)])
+@pytest.mark.parametrize("tile", [None, "3,4,0", "3,64,1", "4,5,1", "4,64,0"])
+def test_tracer_three_step_passes(tile, shape, monkeypatch):
+    if tile:
+        monkeypatch.setenv("J3D_TRACER3_TILE", tile)
+    nx, ny, nz = shape
+    say("tracer three-step passes", tile, shape)
+    t = rand_padded(nx, ny, nz, 25, synth.STREAM_TRACER, 0.0, 1.0)
+    u, v, w = (rand_padded(nx, ny, nz, 25, s, -0.1, 0.1) for s in (6, 7, 8))
+    u[::3, ::2, ::5] = 0.0
+    v[1::4, ::3, ::2] = -0.0
+    w[nz // 2, ny // 2, nx // 2] = np.nan  # a NaN transport gives a zero flux
+    t[nz // 3, ny // 3, nx // 3] = np.inf
+    r = rand_padded(nx, ny, nz, 25, synth.STREAM_RVOL, 0.5, 1.5)
+    fields = [j3d.FArray.from_numpy(a, ld_extra=3, plane_extra=5) for a in (u, v, w, r)]
+    for niter in (3, 4, 6, 8):
+        want = oracle.tracer_advection(t, u, v, w, r, niter)
+        da, db = (j3d.FArray.from_numpy(t, ld_extra=3, plane_extra=5) for _ in range(2))
+        j3d.tracer_advection(da, db, *fields, niter)
+        torch.cuda.synchronize()
+        got = (da if niter % 2 == 0 else db).to_numpy()
+        assert np.array_equal(got, want, equal_nan=True), niter
+
+
+@pytest.mark.parametrize("shape", [(64, 64, 64), (130, 70, 33), (300, 20, 7), (9, 200, 50), (65, 17, 260)])
+def test_advection_default_shapes(shape):
+    """The shapes that the library takes by size: the momentum advection and
+    single tracer steps."""
+    nx, ny, nz = shape
+    say("advection default shapes", shape)
+    u, v, w = (rand_padded(nx, ny, nz, 26, s, -0.1, 0.1) for s in (6, 7, 8))
+    want = oracle.pw_advection(u, v, w, 0.3, 0.11, 1.7)
+    ins = [j3d.FArray.from_numpy(a) for a in (u, v, w)]
+    outs = [j3d.FArray.empty(nx, ny, nz) for _ in range(3)]
+    j3d.pw_advection(*ins, *outs, 0.3, 0.11, 1.7)
+    torch.cuda.synchronize()
+    for o, wt in zip(outs, want):
+        assert np.array_equal(o.to_numpy()[1:-1, 1:-1, 1:-1], wt[1:-1, 1:-1, 1:-1])
+    t = rand_padded(nx, ny, nz, 26, synth.STREAM_TRACER, 0.0, 1.0)
+    r = rand_padded(nx, ny, nz, 26, synth.STREAM_RVOL, 0.5, 1.5)
+    da, db = j3d.FArray.from_numpy(t), j3d.FArray.from_numpy(t)
+    j3d.tracer_advection(da, db, *ins, j3d.FArray.from_numpy(r), 2)
+    torch.cuda.synchronize()
+    assert np.array_equal(da.to_numpy(), oracle.tracer_advection(t, u, v, w, r, 2))
