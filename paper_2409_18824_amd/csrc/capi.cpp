@@ -531,7 +531,7 @@ static int reduce_vec(const double* x, const double* y, int64_t n, uint32_t flag
   hipStream_t st = static_cast<hipStream_t>(stream);
   Scratch* s = nullptr;
   J3D_TRY(get_scratch(st, &s));
-  J3D_TRY(ensure_partials(s, (size_t)sum_blocks(n)));
+  J3D_TRY(ensure_partials(s, (size_t)sum_blocks(n) + kSumWaves));
   double* dst = host ? &s->ctl->value : out;
   J3D_HIP(launch_sum(x, y, n, s->partials, dst, st));
   if (host) {

@@ -182,8 +182,10 @@ hipError_t launch_reduce_batch(const double* partials, const GridArgs* table, in
 
 // sum / dot_product of FP64 vectors (y null: sum of x).  Blocks of the
 // fixed partition of n (sum_blocks(n) partial slots, at most kSumMaxBlocks),
-// then the fixed-pattern sum of the partials into *out (device).
+// then the fixed-pattern sum of the partials into *out (device); partials
+// holds kSumWaves slots more for it.
 constexpr int kSumMaxBlocks = 65536;
+constexpr int kSumWaves = 16;
 long long sum_chunk(long long n);
 int sum_blocks(long long n);
 hipError_t launch_sum(const double* x, const double* y, long long n, double* partials, double* out,

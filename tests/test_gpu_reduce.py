@@ -103,3 +103,16 @@ def test_rejects_bad_tensors():
     with pytest.raises(ValueError):
         j3d.j3d_dot(x, x[:5])
     assert j3d.j3d_sum(x[:0]) == 0.0
+
+
+@pytest.mark.parametrize("nb", [32767, 32768, 32769, 49151, 65535, 65536])
+def test_sum_of_many_partials(nb):
+    """Around the size from which 16 workgroups add the partials, and with a
+    ragged last round of them: integer data, so the result is exact."""
+    n = (nb - 1) * STEP + 5
+    say("sum of partials", nb)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    x = torch.randint(-1000, 1001, (n,), device="cuda", generator=g, dtype=torch.int64)
+    want = int(x.sum().item())
+    assert j3d.j3d_sum(x.to(torch.float64)) == want
