@@ -28,6 +28,8 @@ struct GridArgs {
   int planes;       // z-planes per tile
   int id;           // index of this grid's flags and norms in per-grid arrays
   double h2;        // h*h in FP64
+  double h2_zh, h2_zl;  // 1 / h2 in two parts (see OverH2)
+  unsigned h2_span;     // exponents of dividends that may use them; 0: none
   float h2f;        // (float)(h*h)
   int order;        // tile order: 0 XCD-blocked, 1 as launched, 2 chunked per XCD
   int chunk;        // order 2: tiles per XCD chunk
@@ -119,14 +121,16 @@ int persistent_grid(const TileCfg& c);
 hipError_t launch_pass_one(int dtype, unsigned flags, const TileCfg& c, const GridArgs& g,
                            double* partials, const int* done, hipStream_t st);
 
-// The check of the previous pass, reduced by one extra workgroup of a
-// one-sweep pass instead of by a kernel of its own: the sum of
-// partials[0 .. n) in the order of the reduction kernels (launch_reduce_*:
-// 1024 threads, thread q adding slots q, q + 1024, ... in turn, then each
-// wavefront's butterfly, then the 16 wavefront sums in order), then what
-// launch_reduce_count does with it: hist[*qnext] = sqrt(sum), *done and
-// *conv_at set when it is not finite or at most rtol * *normf (*nonfinite
-// too when not finite), *qnext advanced.  partials == nullptr: no check.
+// The checks of the previous pass (one, or three of a three-sweep pass with
+// the partials of tile t interleaved, partials[3*t + i] that of check i),
+// reduced by one extra workgroup of a pass instead of by a kernel of its own:
+// each the sum of its partials in the order of the reduction kernels
+// (launch_reduce_*: 1024 threads, thread q adding slots q, q + 1024, ... in
+// turn, then each wavefront's butterfly, then the 16 wavefront sums in order),
+// then what launch_reduce_count does with it, check after check: hist[*qnext]
+// = sqrt(sum), *done and *conv_at set when it is not finite or at most rtol *
+// *normf (*nonfinite too when not finite; the checks after it are dropped),
+// *qnext advanced.  partials == nullptr: no checks.
 struct PreReduce {
   const double* partials;
   int n;
@@ -145,6 +149,12 @@ struct PreReduce {
 // pass writes.
 hipError_t launch_pass_one_pre(int dtype, unsigned flags, const TileCfg& c, const GridArgs& g,
                                double* partials, const int* done, const PreReduce& pr, hipStream_t st);
+
+// A three-sweep pass (F_WRITE) that leaves the residuals of all three of its
+// input and intermediate iterates in partials[3*t + i], with the previous
+// such pass's three checks reduced on the side likewise.
+hipError_t launch_sweep3_checks(const TileCfg& c, const GridArgs& g, double* partials, const int* done,
+                                const PreReduce& pr, hipStream_t st);
 
 // Launch one pass over a table of grids in device memory (tile0 ascending,
 // tiles of grid g are [tile0[g], tile0[g] + tx*ty*tz)).  done, if not
@@ -165,8 +175,9 @@ hipError_t launch_reduce_one(const double* partials, int part0, int n, double* o
 
 // The solve drivers' check: sum of partials[0 .. n) -> sqrt -> hist[*qnext];
 // convergence test against rtol * (*normf) as launch_reduce_one with
-// s = *qnext; then *qnext += 1.  Nothing happens once *done != 0.
-hipError_t launch_reduce_count(const double* partials, int n, double* hist, const double* normf,
+// s = *qnext; then *qnext += 1.  Nothing happens once *done != 0.  checks = 3:
+// three checks in a row from the interleaved partials of a three-sweep pass.
+hipError_t launch_reduce_count(int checks, const double* partials, int n, double* hist, const double* normf,
                                double rtol, int* done, long long* conv_at, int* nonfinite,
                                long long* qnext, hipStream_t st);
 

@@ -32,18 +32,20 @@ constexpr int SUM_UNROLL = 8;
 
 // Thread q adds slots q, q + 1024, q + 2048, ... in that order (loads are
 // issued 16 at a time so they overlap, the additions stay in order), then the
-// wavefront butterfly and the 16 wavefront sums in wave order.
+// wavefront butterfly and the 16 wavefront sums in wave order.  Slot m is
+// p[m * STRIDE].
+template <int STRIDE = 1>
 __device__ __forceinline__ double reduce_slots(const double* __restrict__ p, int n, double* s) {
   double a = 0.0;
   int m = threadIdx.x;
   for (; m + (RED_UNROLL - 1) * RED_THREADS < n; m += RED_UNROLL * RED_THREADS) {
     double v[RED_UNROLL];
 #pragma unroll
-    for (int u = 0; u < RED_UNROLL; ++u) v[u] = p[m + u * RED_THREADS];
+    for (int u = 0; u < RED_UNROLL; ++u) v[u] = p[(m + u * RED_THREADS) * STRIDE];
 #pragma unroll
     for (int u = 0; u < RED_UNROLL; ++u) a += v[u];
   }
-  for (; m < n; m += RED_THREADS) a += p[m];
+  for (; m < n; m += RED_THREADS) a += p[m * STRIDE];
   a = wave_sum(a);
   if ((threadIdx.x & (WAVE - 1)) == 0) s[threadIdx.x / WAVE] = a;
   __syncthreads();
@@ -77,25 +79,21 @@ __global__ void __launch_bounds__(RED_THREADS)
 // As k_reduce_one for the solve drivers' checks, with the check index kept
 // on the device: check *qnext goes to hist[*qnext], then *qnext advances.
 // Every check of a replayed graph chunk is therefore the same kernel with the
-// same arguments.
+// same arguments.  CHECKS = 3: three checks in a row from interleaved
+// partials, those after a converged one dropped.
+template <int CHECKS>
 __global__ void __launch_bounds__(RED_THREADS)
     k_reduce_count(const double* __restrict__ partials, int n, double* hist, const double* normf,
                    double rtol, int* done, long long* conv_at, int* nonfinite, long long* qnext) {
   if (*done != 0) return;
-  __shared__ double sred[RED_WAVES];
-  const double tot = reduce_slots(partials, n, sred);
-  if (threadIdx.x == 0) {
-    const long long q = *qnext;
-    const double r = sqrt(tot);
-    hist[q] = r;
-    const bool bad = !isfinite(r);
-    if (bad || r <= rtol * (*normf)) {
-      *done = 1;
-      *conv_at = q;
-      if (bad) *nonfinite = 1;
-    }
-    *qnext = q + 1;
-  }
+  __shared__ double sred[CHECKS][RED_WAVES];
+  const long long q = *qnext;
+  const double nf = *normf;
+  double tot[CHECKS];
+#pragma unroll
+  for (int i = 0; i < CHECKS; ++i) tot[i] = reduce_slots<CHECKS>(partials + i, n, sred[i]);
+  if (threadIdx.x == 0)
+    *qnext = sweep_detail::count_checks<CHECKS>(tot, q, hist, nf, rtol, done, conv_at, nonfinite);
 }
 
 __global__ void __launch_bounds__(RED_THREADS)
@@ -410,6 +408,12 @@ hipError_t launch_sweep3_one(int dtype, unsigned flags, const TileCfg& c, const 
   return sweep_detail::dispatch_sweep3_f32(flags, c, g, partials, done, st);
 }
 
+hipError_t launch_sweep3_checks(const TileCfg& c, const GridArgs& g, double* partials, const int* done,
+                                const PreReduce& pr, hipStream_t st) {
+  if (!tile3_cfg_supported(J3D_F64, c)) return hipErrorInvalidValue;
+  return sweep_detail::dispatch_sweep3_checks(c, g, partials, done, pr, st);
+}
+
 hipError_t launch_sweep3_batch(int dtype, unsigned flags, const TileCfg& c, const GridArgs* table, int ngrids,
                                int ntiles, double* partials, const int* done, hipStream_t st,
                                const TileSlot* slots, int nslots) {
@@ -489,11 +493,15 @@ hipError_t launch_reduce_one(const double* partials, int part0, int n, double* o
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_count(const double* partials, int n, double* hist, const double* normf,
+hipError_t launch_reduce_count(int checks, const double* partials, int n, double* hist, const double* normf,
                                double rtol, int* done, long long* conv_at, int* nonfinite,
                                long long* qnext, hipStream_t st) {
-  hipLaunchKernelGGL(k_reduce_count, dim3(1), dim3(RED_THREADS), 0, st, partials, n, hist, normf, rtol,
-                     done, conv_at, nonfinite, qnext);
+  if (checks == 3)
+    hipLaunchKernelGGL(k_reduce_count<3>, dim3(1), dim3(RED_THREADS), 0, st, partials, n, hist, normf, rtol,
+                       done, conv_at, nonfinite, qnext);
+  else
+    hipLaunchKernelGGL(k_reduce_count<1>, dim3(1), dim3(RED_THREADS), 0, st, partials, n, hist, normf, rtol,
+                       done, conv_at, nonfinite, qnext);
   return hipGetLastError();
 }
 

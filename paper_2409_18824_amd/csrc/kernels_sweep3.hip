@@ -1,6 +1,6 @@
 // Instantiations of the FP64 three-sweep pass: plain sweeps, optionally
-// with the fused residual of the input iterate or of either intermediate
-// iterate.
+// with the fused residual of the input iterate, of either intermediate
+// iterate, or of all three.
 #include "sweep3.h"
 
 namespace j3d {
@@ -13,6 +13,19 @@ hipError_t dispatch_sweep3_f64(unsigned flags, const TileCfg& c, const GridArgs&
     case F_WRITE | F_RES: return by_shape3<double, F_WRITE | F_RES>(c, g, partials, done, st);
     case F_WRITE | F_RES1: return by_shape3<double, F_WRITE | F_RES1>(c, g, partials, done, st);
     case F_WRITE | F_RES2: return by_shape3<double, F_WRITE | F_RES2>(c, g, partials, done, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t dispatch_sweep3_checks(const TileCfg& c, const GridArgs& g, double* partials, const int* done,
+                                  const PreReduce& pr, hipStream_t st) {
+  switch (c.rows * 100 + c.variant) {
+    case 220: return go3_checks<2, 20>(g, partials, done, pr, st);
+    case 406: return go3_checks<4, 6>(g, partials, done, pr, st);
+    case 420: return go3_checks<4, 20>(g, partials, done, pr, st);
+    case 806: return go3_checks<8, 6>(g, partials, done, pr, st);
+    case 820: return go3_checks<8, 20>(g, partials, done, pr, st);
+    case 1606: return go3_checks<16, 6>(g, partials, done, pr, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -189,6 +189,9 @@ GridArgs make_args(const Field* u, const Field* o, const Field* f, const Field* 
   g.tile0 = tile0;
   g.planes = c.planes;
   g.h2 = h * h;
+  g.h2_zh = 1.0 / g.h2;
+  g.h2_zl = std::fma(-g.h2, g.h2_zh, 1.0) * g.h2_zh;
+  g.h2_span = g.h2 >= 0x1p-100 && g.h2 <= 0x1p100 ? 1800u << 20 : 0u;
   g.h2f = static_cast<float>(h * h);
   g.order = c.order;
   g.chunk = (g.tiles_x * g.tiles_y + 7) / 8;

@@ -100,15 +100,24 @@ void fill_result(j3d_solve_result* r, long long sweeps, double resid, const std:
 // FP64 mode
 // ---------------------------------------------------------------------
 
-// Solves that check after every sweep on grids of at most 2^24 points,
-// where a check's reduction kernel costs about half a sweep: each pass's
-// check is reduced by an extra workgroup of the next pass
-// (launch_pass_one_pre).  That pass runs before the check's verdict is
-// known, so the iterates rotate through three arrays (the pass after a
-// converged check writes the array of the iterate before it, never the
-// converged one) and the per-tile partials through two.  Same kernels,
-// same reduction order, same results as the schedule with a reduction
-// kernel per check.  J3D_SOLVE_FUSED_CHECKS=0 turns it off.
+// Solves that check after every sweep run in three-sweep passes that leave
+// the residuals of all three of their iterates, but on small grids, where a
+// pass is a chain of latencies, in one-sweep passes (us per sweep in passes of
+// three / one, checks included: 64^3 4.4 / 4.1, 88^3 5.8 / 10.0, 128^3 9.2 /
+// 20, 256^3 59 / 94, 512^3 289 / 627).
+bool three_checks_per_pass(long long c, long long points) {
+  return c == 1 && points > (1LL << 18);
+}
+
+// On grids of at most 2^24 points, where a reduction kernel per pass costs up
+// to half of it, the checks of a pass are reduced by an extra workgroup of the
+// next one (launch_pass_one_pre, launch_sweep3_checks).  That pass runs before
+// their verdict is known, so the iterates rotate through three arrays (the
+// pass after a converged check writes neither the array of the iterate that
+// the checked one was formed from nor that iterate's own) and the per-tile
+// partials through two.  Same kernels, same reduction order, same results as
+// the schedule with a reduction kernel per pass.  J3D_SOLVE_FUSED_CHECKS=0
+// turns it off.
 bool fused_checks_apply(long long c, long long points) {
   const char* e = std::getenv("J3D_SOLVE_FUSED_CHECKS");
   if (e != nullptr && std::atoi(e) == 0) return false;
@@ -120,8 +129,12 @@ int solve_fp64_fused_checks(const Field& u, const Field& f, double h, const j3d_
   Scratch* s = nullptr;
   J3D_TRY(get_scratch(st, &s));
   const TileCfg cfg = default_cfg(J3D_F64, u.nx(), u.ny(), u.nz());
+  const TileCfg cfg2 = default_cfg2(J3D_F64, u.nx(), u.ny(), u.nz());
+  const TileCfg cfg3 = default_cfg3(J3D_F64, u.nx(), u.ny(), u.nz());
   const long long S = o.max_sweeps;
   const long long points = (long long)u.nx() * u.ny() * u.nz();
+  const int L = three_checks_per_pass(1, points) ? 3 : 1;  // sweeps and checks per pass
+  const long long P = S / L;                               // passes; the rest one by one
 
   // u, and two arrays of u's layout in the work buffer, all with u's halo
   const size_t span = (u.span_bytes() + 255) / 256 * 256;
@@ -132,51 +145,66 @@ int solve_fp64_fused_checks(const Field& u, const Field& f, double h, const j3d_
   J3D_HIP(hipMemcpyAsync(buf3[1].base, u.base, u.span_bytes(), hipMemcpyDeviceToDevice, st));
   J3D_HIP(hipMemcpyAsync(buf3[2].base, u.base, u.span_bytes(), hipMemcpyDeviceToDevice, st));
 
-  GridArgs one[3], resid[3];
+  GridArgs one[3], two[3], three[3], resid[3];
   for (int b = 0; b < 3; ++b) {
     one[b] = make_args(&buf3[b], &buf3[(b + 1) % 3], &f, nullptr, nullptr, h, cfg, 0);
+    two[b] = make_args2(&buf3[b], &buf3[(b + 1) % 3], &f, nullptr, h, cfg2, 0);
+    three[b] = make_args3(&buf3[b], &buf3[(b + 1) % 3], &f, nullptr, h, cfg3, 0);
     resid[b] = make_args(&buf3[b], nullptr, &f, nullptr, nullptr, h, cfg, 0);
   }
-  const int nt = one[0].tiles_x * one[0].tiles_y * one[0].tiles_z;
-  const size_t ntp = ((size_t)nt + 31) / 32 * 32;
+  const int nt1 = one[0].tiles_x * one[0].tiles_y * one[0].tiles_z;
+  const int nt3 = three[0].tiles_x * three[0].tiles_y * three[0].tiles_z;
+  const int nt = L == 3 ? nt3 : nt1;
+  const size_t ntp = ((size_t)std::max(nt1, L * nt) + 31) / 32 * 32;
   J3D_TRY(ensure_partials(s, 2 * ntp));
   double* part[2] = {s->partials, s->partials + ntp};
   J3D_TRY(ensure_hist(s, (size_t)S + 1));
   J3D_HIP(hipMemsetAsync(s->ctl, 0, sizeof(Control), st));
   J3D_TRY(norm_f(f, cfg, s, st));
   int* done = &s->ctl->done;
-  auto pre_of = [&](long long q) {  // the reduction of check q (the partials of pass q)
-    PreReduce pr{part[q & 1], nt, s->hist, &s->ctl->normf, o.rtol, done, &s->ctl->conv_at,
-                 &s->ctl->nonfinite, &s->ctl->qnext};
-    return pr;
+  auto pre_of = [&](long long p) {  // the reduction of the checks of pass p
+    return PreReduce{p >= 0 ? part[p & 1] : nullptr, nt, s->hist, &s->ctl->normf, o.rtol, done, &s->ctl->conv_at,
+                     &s->ctl->nonfinite, &s->ctl->qnext};
   };
-  // pass p: iterate p (array p % 3) -> p + 1, residual of iterate p into
-  // part[p % 2], the check of pass p - 1 reduced on the side
+  // pass p: iterate L p (array p % 3) -> L p + L, the residuals of its L input
+  // iterates into part[p % 2], the checks of pass p - 1 reduced on the side
   auto pass = [&](long long p, hipStream_t q) -> int {
-    const int b = (int)(p % 3);
-    if (p == 0) {
-      J3D_HIP(launch_pass_one(J3D_F64, F_WRITE | F_RES, cfg, one[b], part[0], done, q));
-    } else {
-      J3D_HIP(launch_pass_one_pre(J3D_F64, F_WRITE | F_RES, cfg, one[b], part[p & 1], done, pre_of(p - 1), q));
-    }
+    if (L == 3)
+      J3D_HIP(launch_sweep3_checks(cfg3, three[p % 3], part[p & 1], done, pre_of(p - 1), q));
+    else
+      J3D_HIP(launch_pass_one_pre(J3D_F64, F_WRITE | F_RES, cfg, one[p % 3], part[p & 1], done, pre_of(p - 1), q));
     return J3D_OK;
   };
-  const long long chunk = chunk_sweeps(points, 24.0, 6);  // a multiple of the 3 x 2 rotation
+  auto count = [&](int checks, const double* partials, int nt) -> int {
+    J3D_HIP(launch_reduce_count(checks, partials, nt, s->hist, &s->ctl->normf, o.rtol, done, &s->ctl->conv_at,
+                                &s->ctl->nonfinite, &s->ctl->qnext, st));
+    return J3D_OK;
+  };
+  // passes, a multiple of the 3 x 2 rotation
+  const long long chunk = chunk_sweeps(points, 24.0 / L, 6 * L) / L;
   long long p = 0;
   int slot = 0;
   bool seen = false;
-  if (S > 0) {
+  auto poll = [&]() -> int {
+    J3D_TRY(publish_done(s, slot, st));
+    if (slot > 0) J3D_TRY(poll_done(s, slot - 1, &seen));
+    ++slot;
+    return J3D_OK;
+  };
+  if (P > 0) {
     J3D_TRY(pass(0, st));
     p = 1;
   }
   // whole chunks starting at passes 1, 1 + M, ... replayed from one graph
-  const long long M = std::min(chunk, (S - 1) / 2 / 6 * 6);
-  if (S > 0 && M > 0) {
+  const long long M = std::min(chunk, (P - 1) / 2 / 6 * 6);
+  if (P > 0 && M > 0) {
     std::string key = "fp64-fused";
     auto add = [&key](const void* x, size_t n) { key.append(static_cast<const char*>(x), n); };
     add(one, sizeof one);
+    add(three, sizeof three);
     add(&cfg, sizeof cfg);
-    const long long meta[3] = {M, nt, (long long)ntp};
+    add(&cfg3, sizeof cfg3);
+    const long long meta[4] = {L, M, nt, (long long)ntp};
     add(meta, sizeof meta);
     const void* ptrs[3] = {s->partials, s->hist, s->ctl};
     add(ptrs, sizeof ptrs);
@@ -186,30 +214,31 @@ int solve_fp64_fused_checks(const Field& u, const Field& f, double h, const j3d_
       for (long long i = 1; i <= M; ++i) J3D_TRY(pass(i, q));
       return J3D_OK;
     }, &exec));
-    while (p + M <= S && !seen) {
+    while (p + M <= P && !seen) {
       J3D_HIP(hipGraphLaunch(exec, st));
       p += M;
-      J3D_TRY(publish_done(s, slot, st));
-      if (slot > 0) J3D_TRY(poll_done(s, slot - 1, &seen));
-      ++slot;
+      J3D_TRY(poll());
     }
   }
-  while (p < S && !seen) {
-    const long long end = std::min(S, p + chunk);
+  while (p < P && !seen) {
+    const long long end = std::min(P, p + chunk);
     for (; p < end; ++p) J3D_TRY(pass(p, st));
-    J3D_TRY(publish_done(s, slot, st));
-    if (slot > 0) J3D_TRY(poll_done(s, slot - 1, &seen));
-    ++slot;
+    J3D_TRY(poll());
   }
-  // the residual of the last iterate (check S), which also reduces check
-  // S - 1; skipped, like every kernel after it, once a check converged
-  const int bl = (int)(S % 3);
-  if (S > 0)
-    J3D_HIP(launch_pass_one_pre(J3D_F64, F_RES, cfg, resid[bl], part[S & 1], done, pre_of(S - 1), st));
-  else
-    J3D_HIP(launch_pass_one(J3D_F64, F_RES, cfg, resid[bl], part[0], done, st));
-  J3D_HIP(launch_reduce_count(part[S & 1], nt, s->hist, &s->ctl->normf, o.rtol, done, &s->ctl->conv_at,
-                              &s->ctl->nonfinite, &s->ctl->qnext, st));
+  // The residual of the last iterate (check S), with the last pass's check
+  // reduced on the side; after three-sweep passes their checks, the sweeps left
+  // over with theirs, and then check S.  Each kernel is skipped once a check
+  // converged.
+  p = P;
+  if (L == 3 && P > 0) J3D_TRY(count(3, part[(P - 1) & 1], nt));
+  for (; p < P + S % L; ++p) {
+    J3D_HIP(launch_pass_one(J3D_F64, F_WRITE | F_RES, cfg, one[p % 3], part[0], done, st));
+    J3D_TRY(count(1, part[0], nt1));
+  }
+  const int bl = (int)(p % 3);
+  double* last = part[P & 1];
+  J3D_HIP(launch_pass_one_pre(J3D_F64, F_RES, cfg, resid[bl], last, done, pre_of(L == 1 ? P - 1 : -1), st));
+  J3D_TRY(count(1, last, nt1));
   Control ctl;
   J3D_TRY(read_control(s, &ctl, st));
   long long sweeps, nh;
@@ -217,7 +246,13 @@ int solve_fp64_fused_checks(const Field& u, const Field& f, double h, const j3d_
   if (ctl.done) {
     sweeps = ctl.conv_at;
     nh = ctl.conv_at + 1;
-    at = (int)(ctl.conv_at % 3);
+    // an iterate inside a pass is formed again from the pass's input
+    const bool tail = sweeps >= L * P;
+    at = (int)((tail ? P + (sweeps - L * P) : sweeps / L) % 3);
+    const int again = tail ? 0 : (int)(sweeps % L);
+    if (again == 1) J3D_HIP(launch_pass_one(J3D_F64, F_WRITE, cfg, one[at], nullptr, nullptr, st));
+    if (again == 2) J3D_HIP(launch_sweep2_one(J3D_F64, F_WRITE, cfg2, two[at], nullptr, nullptr, st));
+    if (again > 0) at = (at + 1) % 3;
   } else {
     sweeps = S;
     nh = S + 1;
@@ -236,7 +271,9 @@ int solve_fp64_fused_checks(const Field& u, const Field& f, double h, const j3d_
 
 int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o,
                j3d_solve_result* res, hipStream_t st) {
-  if (forced_step() == 0 && fused_checks_apply(o.check_every, (long long)u.nx() * u.ny() * u.nz()))
+  // (a three-sweep pass needs planes below 4 GiB)
+  const bool fit3 = plane_fits_u32(u) && plane_fits_u32(f);
+  if (forced_step() == 0 && fit3 && fused_checks_apply(o.check_every, (long long)u.nx() * u.ny() * u.nz()))
     return solve_fp64_fused_checks(u, f, h, o, res, st);
   Scratch* s = nullptr;
   J3D_TRY(get_scratch(st, &s));
@@ -247,24 +284,25 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   const long long c = o.check_every;
   const long long points = (long long)u.nx() * u.ny() * u.nz();
   // Passes of `step` sweeps: three, or two for checks after every second
-  // sweep and one for checks after every sweep.  Three-sweep passes run
+  // sweep.  Three-sweep passes run
   // straight through the sweeps: the residual of a check is fused into the
   // pass that forms its iterate, at that stage of the pass, whose input
   // stays in its array until the check's verdict is known (every later
   // kernel skips its work once a check has converged), so the checked
-  // iterate can be formed again.  (At the end of a range a shorter pass
-  // stops before a check it would hold past its input.)  With a forced
-  // step of one or two a check group of c sweeps opens with one pass of c
+  // iterate can be formed again; with checks after every sweep they carry
+  // all three residuals.  (At the end of a range a shorter pass stops before
+  // a check it would hold past its input.)  With a forced step of one or two a check group of c sweeps opens with one pass of c
   // mod step sweeps (none when step divides c), which carries the check's
   // residual, and continues in passes of step sweeps.
-  // (w has u's layout; a three-sweep pass needs planes below 4 GiB)
-  const bool fit3 = plane_fits_u32(u) && plane_fits_u32(f);
-  long long step = forced_step() != 0 ? forced_step() : std::min<long long>(c, 3);
+  // (w has u's layout)
+  const bool all3 = forced_step() == 0 && fit3 && three_checks_per_pass(c, points);
+  long long step = forced_step() != 0 ? forced_step() : all3 ? 3 : std::min<long long>(c, 3);
   if (step == 3 && !fit3) step = 2;
   const long long lead = c % step;
   struct Pass {
     int len;    // sweeps
-    int stage;  // the residual it carries is that of the iterate after this many of them; -1: none
+    int stage;  // the residual it carries is that of the iterate after this many of them; -1: none,
+                // 3: those of its input and both intermediate iterates
   };
   auto next_pass = [&](long long sw, long long to) -> Pass {
     if (step != 3) {
@@ -272,6 +310,7 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
       const long long len = std::min(p == 0 && lead != 0 ? lead : step, c - p);
       return Pass{(int)std::min(len, to - sw), p == 0 ? 0 : -1};
     }
+    if (all3) return to - sw >= 3 ? Pass{3, 3} : Pass{1, 0};
     int len = (int)std::min<long long>(3, to - sw), stage = -1;
     for (int o = 0; o < len; ++o) {
       if ((sw + o) % c != 0) continue;
@@ -284,8 +323,9 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
     return Pass{len, stage};
   };
   // the schedule repeats after `period` sweeps
-  const long long period = step == 3 && c >= 3 ? std::lcm(c, 3LL) : c;
-  const long long period_passes = step == 3 ? (c >= 3 ? period / 3 : 1) : (lead != 0 ? 1 : 0) + c / step;
+  const bool straight = step == 3 && (c >= 3 || all3);
+  const long long period = straight ? std::lcm(c, 3LL) : c;
+  const long long period_passes = straight ? period / 3 : step == 3 ? 1 : (lead != 0 ? 1 : 0) + c / step;
 
   // The second ping-pong array has u's layout and starts as a copy of u
   // (which gives it the same halo).
@@ -305,7 +345,7 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   const int nt1 = one[0].tiles_x * one[0].tiles_y * one[0].tiles_z;
   const int nt2 = two[0].tiles_x * two[0].tiles_y * two[0].tiles_z;
   const int nt3 = three[0].tiles_x * three[0].tiles_y * three[0].tiles_z;
-  J3D_TRY(ensure_partials(s, std::max(nt1, std::max(nt2, nt3))));
+  J3D_TRY(ensure_partials(s, std::max(nt1, std::max(nt2, all3 ? 3 * nt3 : nt3))));
   const long long nchecks = S / c + 1;
   J3D_TRY(ensure_hist(s, (size_t)nchecks));
 
@@ -326,7 +366,10 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
       const unsigned fl =
           F_WRITE | (ps.stage < 0 ? 0u : ps.stage == 0 ? F_RES : ps.stage == 1 ? F_RES1 : F_RES2);
       int nt;
-      if (ps.len == 3) {
+      if (ps.stage == 3) {
+        J3D_HIP(launch_sweep3_checks(cfg3, three[b], s->partials, done, PreReduce{}, q));
+        nt = nt3;
+      } else if (ps.len == 3) {
         J3D_HIP(launch_sweep3_one(J3D_F64, fl, cfg3, three[b], s->partials, done, q));
         nt = nt3;
       } else if (ps.len == 2) {
@@ -338,8 +381,8 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
       }
       sw += ps.len;
       if (ps.stage >= 0)
-        J3D_HIP(launch_reduce_count(s->partials, nt, s->hist, &s->ctl->normf, o.rtol, done, &s->ctl->conv_at,
-                                    &s->ctl->nonfinite, &s->ctl->qnext, q));
+        J3D_HIP(launch_reduce_count(ps.stage == 3 ? 3 : 1, s->partials, nt, s->hist, &s->ctl->normf, o.rtol, done,
+                                    &s->ctl->conv_at, &s->ctl->nonfinite, &s->ctl->qnext, q));
       b = 1 - b;
     }
     return J3D_OK;
@@ -349,7 +392,8 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   auto track = [&](long long from, long long to, int b) -> int {
     for (long long sw = from; sw < to;) {
       const Pass ps = next_pass(sw, to);
-      if (ps.stage >= 0) which_at[(size_t)((sw + ps.stage) / c)] = (unsigned char)(2 * ps.stage + b);
+      for (int at = 0; at < 3; ++at)
+        if (ps.stage == at || ps.stage == 3) which_at[(size_t)((sw + at) / c)] = (unsigned char)(2 * at + b);
       sw += ps.len;
       b = 1 - b;
     }
@@ -404,7 +448,7 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
     if (S % c == 0) which_at[(size_t)(S / c)] = (unsigned char)cur;
     J3D_HIP(launch_pass_one(J3D_F64, F_RES, cfg, resid[cur], s->partials, done, st));
     if (S % c == 0)  // check S / c: the counter holds exactly that index here
-      J3D_HIP(launch_reduce_count(s->partials, nt1, s->hist, &s->ctl->normf, o.rtol, done, &s->ctl->conv_at,
+      J3D_HIP(launch_reduce_count(1, s->partials, nt1, s->hist, &s->ctl->normf, o.rtol, done, &s->ctl->conv_at,
                                   &s->ctl->nonfinite, &s->ctl->qnext, st));
     else
       J3D_HIP(launch_reduce_one(s->partials, 0, nt1, &s->ctl->value, nullptr, 0.0, 0, done, nullptr,
@@ -523,7 +567,7 @@ int solve_mixed(const Field& u, const Field& f, double h, const j3d_solve_opts& 
   // defect step).  Units with the same m are the same kernel sequence.
   auto unit = [&](long long m, hipStream_t q) -> int {
     J3D_HIP(launch_pass_one(J3D_F64, F_RES | F_R32, cd, defect, s->partials, done, q));
-    J3D_HIP(launch_reduce_count(s->partials, nt, s->hist, &s->ctl->normf, o.rtol, done, &s->ctl->conv_at,
+    J3D_HIP(launch_reduce_count(1, s->partials, nt, s->hist, &s->ctl->normf, o.rtol, done, &s->ctl->conv_at,
                                 &s->ctl->nonfinite, &s->ctl->qnext, q));
     if (m == 0) return J3D_OK;
     if (m <= step) {

@@ -162,6 +162,53 @@ __device__ __forceinline__ float div6_fused(float x) {
 __device__ __forceinline__ bool div6_small(double x) { return __builtin_fabs(x) < 0x1p-1000; }
 __device__ __forceinline__ bool div6_small(float x) { return __builtin_fabsf(x) < 0x1p-100f; }
 
+// Division by h2 = h * h without a division per point: q = x / h2 rounded to
+// nearest, by Markstein's correction (IBM J. Res. Dev. 34(1), 1990) of a
+// quotient that is already within an ulp: with zh = RN(1 / h2) and zl the rest
+// of 1 / h2, p = RN(x zh + RN(x zl)) is off by little more than half an ulp,
+// the remainder x - p h2 is exact in one fused operation, and with zh the
+// correctly rounded reciprocal q = RN(p + (x - p h2) zh) is the IEEE quotient,
+// as long as nothing leaves the normal range: for 2^-900 <= |x| < 2^900 and
+// 2^-100 <= h2 <= 2^100.  Lanes outside it (zeros among them) divide.  Four
+// operations against eleven and a reciprocal: a 200-sweep mixed solve at 256^3,
+// whose defect passes are the residual, takes 4.57 ms against 4.72.
+struct OverH2 {
+  double h2, zh, zl;
+  uint32_t span;  // of the accepted exponents, in the upper word; 0: always divide
+
+  __device__ __forceinline__ explicit OverH2(const GridArgs& g)
+      : h2(g.h2), zh(g.h2_zh), zl(g.h2_zl), span(g.h2_span) {}
+  __device__ __forceinline__ double fused(double x) const {
+    const double p = __builtin_fma(x, zh, x * zl);
+    return __builtin_fma(__builtin_fma(-p, h2, x), zh, p);
+  }
+  __device__ __forceinline__ bool outside(double x) const {
+    const uint32_t hi = static_cast<uint32_t>(__builtin_bit_cast(uint64_t, x) >> 32) & 0x7fffffffu;
+    return hi - ((1023u - 900u) << 20) >= span;
+  }
+  // The residuals f - (6 u - s) / h2 of a row block; act: the rows whose
+  // value is used.
+  template <int RY, typename T>
+  __device__ __forceinline__ void residuals(const T (&f)[RY], const T (&u)[RY], const T (&s)[RY],
+                                            const bool (&act)[RY], double (&res)[RY]) const {
+    double x[RY], q[RY];
+    uint64_t odd = 0;  // lanes whose quotient needs the division
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      x[r] = 6.0 * static_cast<double>(u[r]) - static_cast<double>(s[r]);
+      q[r] = fused(x[r]);
+      odd |= __builtin_amdgcn_ballot_w64(act[r] && outside(x[r]));
+    }
+    if (odd != 0) {
+#pragma unroll
+      for (int r = 0; r < RY; ++r)
+        if (outside(x[r])) q[r] = x[r] / h2;
+    }
+#pragma unroll
+    for (int r = 0; r < RY; ++r) res[r] = static_cast<double>(f[r]) - q[r];
+  }
+};
+
 // Buffer resource for a wave-uniform base address: every load and store of
 // a plane then takes the plane's address in scalar registers and a per-lane
 // 32-bit byte offset that is fixed for the whole tile, so the z march needs
@@ -240,6 +287,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc_n(const void* b, ui
       const_cast<char*>(static_cast<const char*>(b)) + (uint64_t)(uint32_t)kk * z, 0, (int)rec, 0x00020000);
 }
 
+// A solve's flag, read by a vector load whose wait comes after a tile's first
+// loads are issued: asked before them, the flag's trip to memory (another
+// kernel wrote it) stands in front of theirs (a 64^3 pass with a
+// residual takes 3.9 us instead of 4.1; three-sweep passes gain nothing and ask
+// first).  A null pointer is an empty buffer, which reads as zero.
+__device__ __forceinline__ int load_flag(const int* done) {
+  const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<int*>(done), 0, done != nullptr ? 4 : 0, 0x00020000);
+  return static_cast<int>(__builtin_amdgcn_raw_buffer_load_b32(r, 0, 0, 0));
+}
+__device__ __forceinline__ bool is_set(int flag) { return __builtin_amdgcn_readfirstlane(flag) != 0; }
+
 // One tile of the cache-fed variants (x-neighbours from the adjacent lanes,
 // the wavefront's two halo columns from one gather, y-neighbours from
 // registers inside the row block and two edge loads outside it).
@@ -259,7 +317,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc_n(const void* b, ui
 // The arithmetic and its order are those of the LDS variant (same bits).
 template <typename T, int BY, int WX, int VAR, unsigned FL>
 __device__ __forceinline__ void sweep_tile_cf(const GridArgs& g, int t, double* __restrict__ partials,
-                                              Smem<T, BY, WX, VAR>& sm) {
+                                              Smem<T, BY, WX, VAR>& sm, int done) {
   constexpr bool STENCIL = !(FL & (F_FIRST | F_NORM));
   constexpr int RY = rows_per_thread(VAR);
   constexpr int TX = WAVE * WX;
@@ -317,6 +375,7 @@ __device__ __forceinline__ void sweep_tile_cf(const GridArgs& g, int t, double* 
   const uint64_t zu = (uint64_t)g.su_z * ES, zf = (uint64_t)g.sf_z * ES, zo = (uint64_t)g.so_z * ES;
   const uint64_t zr = (uint64_t)g.sr_z * 4, zq = (uint64_t)g.s64_z * 8;
   const T h2 = h2_of<T>(g);
+  [[maybe_unused]] const OverH2 quot(g);  // of the residuals
 
   double acc = 0.0;
   T um[RY], uc[RY];
@@ -403,17 +462,20 @@ __device__ __forceinline__ void sweep_tile_cf(const GridArgs& g, int t, double* 
         s[r] = v;
       }
     }
+    if (FL & F_NORM) {
 #pragma unroll
-    for (int r = 0; r < RY; ++r) {
-      if (FL & F_NORM) {
+      for (int r = 0; r < RY; ++r) {
         const double v = static_cast<double>(L.f[r]) * static_cast<double>(L.f[r]);
         acc += act[r] ? v : 0.0;
       }
-      if (STENCIL && (FL & (F_RES | F_R32))) {
-        const double res = static_cast<double>(L.f[r]) -
-                           (6.0 * static_cast<double>(uc[r]) - static_cast<double>(s[r])) / g.h2;
-        if (FL & F_RES) acc += act[r] ? res * res : 0.0;
-        sr[r] = static_cast<float>(res);
+    }
+    if (STENCIL && (FL & (F_RES | F_R32))) {
+      double res[RY];
+      quot.residuals(L.f, uc, s, act, res);
+#pragma unroll
+      for (int r = 0; r < RY; ++r) {
+        if (FL & F_RES) acc += act[r] ? res[r] * res[r] : 0.0;
+        sr[r] = static_cast<float>(res[r]);
       }
     }
     if (FL & (F_WRITE | F_LAST)) {
@@ -449,6 +511,7 @@ __device__ __forceinline__ void sweep_tile_cf(const GridArgs& g, int t, double* 
   // the step's one wait)
   Loads N, C;
   issue(N, k0);
+  if (is_set(done)) return;
   for (int k = k0; k < k1; ++k) {
     C = N;
     issue(N, min(k + 1, k1 - 1));
@@ -466,7 +529,8 @@ __device__ __forceinline__ void sweep_tile_cf(const GridArgs& g, int t, double* 
 }
 
 // One tile: local tile index t of grid g.  Writes the tile's partial sum
-// (F_RES / F_NORM) to partials[g.tile0 + t].  The cache-fed variants run
+// (F_RES / F_NORM) to partials[g.tile0 + t], unless done (see load_flag) is
+// set.  The cache-fed variants run
 // sweep_tile_cf unless a plane of the grid spans 2^31 bytes or more; this
 // pointer-addressed body serves the LDS variants and those grids.
 //
@@ -479,7 +543,7 @@ __device__ __forceinline__ void sweep_tile_cf(const GridArgs& g, int t, double* 
 // only stores and sums are masked.
 template <typename T, int BY, int WX, int VAR, unsigned FL>
 __device__ __forceinline__ void sweep_tile(const GridArgs& g, int t, double* __restrict__ partials,
-                                           Smem<T, BY, WX, VAR>& sm) {
+                                           Smem<T, BY, WX, VAR>& sm, int done) {
   constexpr bool STENCIL = !(FL & (F_FIRST | F_NORM));
   constexpr bool USE_LDS = (VAR & 1) && STENCIL;
   constexpr int RY = rows_per_thread(VAR);
@@ -488,10 +552,11 @@ __device__ __forceinline__ void sweep_tile(const GridArgs& g, int t, double* __r
   constexpr bool NT = (VAR & 4) != 0;
   if constexpr ((VAR & 1) == 0) {
     if (g.wide_planes == 0) {
-      sweep_tile_cf<T, BY, WX, VAR, FL>(g, t, partials, sm);
+      sweep_tile_cf<T, BY, WX, VAR, FL>(g, t, partials, sm, done);
       return;
     }
   }
+  if (is_set(done)) return;
   const int lane = threadIdx.x;    // column within the tile
   const int wy = threadIdx.y;
   const int tx = t % g.tiles_x;
@@ -535,6 +600,7 @@ __device__ __forceinline__ void sweep_tile(const GridArgs& g, int t, double* __r
   float* __restrict__ pr = g.r32 + (ic + g.sr_y * jc + g.sr_z * k0);
   double* __restrict__ p64 = g.u64 + (ic + g.s64_y * jc + g.s64_z * k0);
   const T h2 = h2_of<T>(g);
+  [[maybe_unused]] const OverH2 quot(g);  // of the residuals
 
   double acc = 0.0;
   T um[RY], uc[RY];
@@ -612,8 +678,8 @@ __device__ __forceinline__ void sweep_tile(const GridArgs& g, int t, double* __r
         acc += act[r] ? v : 0.0;
       } else {
         if (STENCIL && (FL & (F_RES | F_R32))) {
-          const double res = static_cast<double>(fc[r]) -
-                             (6.0 * static_cast<double>(uc[r]) - static_cast<double>(s)) / g.h2;
+          const double x = 6.0 * static_cast<double>(uc[r]) - static_cast<double>(s);
+          const double res = static_cast<double>(fc[r]) - (quot.outside(x) ? x / g.h2 : quot.fused(x));
           if (FL & F_RES) acc += act[r] ? res * res : 0.0;
           if ((FL & F_R32) && act[r]) put<float, NT>(pr + dj[r] * g.sr_y, static_cast<float>(res));
         }
@@ -647,6 +713,30 @@ __device__ __forceinline__ void sweep_tile(const GridArgs& g, int t, double* __r
   __syncthreads();
 }
 
+// What the sums of squares of CHECKS checks in a row mean for a solve: check
+// q + i goes to the history, the first that is not finite or at most rtol *
+// normf ends it.  One thread; returns the index of the next check.
+template <int CHECKS>
+__device__ __forceinline__ long long count_checks(const double (&tot)[CHECKS], long long q, double* hist, double normf,
+                                                  double rtol, int* done, long long* conv_at, int* nonfinite) {
+  bool go = true;
+#pragma unroll
+  for (int i = 0; i < CHECKS; ++i) {
+    const double r = sqrt(tot[i]);
+    if (!go) continue;
+    hist[q] = r;
+    const bool bad = !isfinite(r);
+    if (bad || r <= rtol * normf) {
+      *done = 1;
+      *conv_at = q;
+      if (bad) *nonfinite = 1;
+      go = false;
+    }
+    ++q;
+  }
+  return q;
+}
+
 // The previous pass's check (PreReduce), reduced by one workgroup of any
 // size that divides 1024 into the same bits as the 1024-thread reduction
 // kernels: thread t stands in for threads t, t + T, t + 2T, ... of those,
@@ -657,6 +747,8 @@ __device__ __forceinline__ void pre_reduce(const PreReduce& pr) {
   __shared__ double ws[VT / WAVE];
   const int T = blockDim.x * blockDim.y;
   const int t = threadIdx.y * blockDim.x + threadIdx.x;
+  const long long q0 = *pr.qnext;  // (on their way together with the partials)
+  const double normf = *pr.normf;
   for (int q = t; q < VT; q += T) {
     double a = 0.0;
     for (int m = q; m < pr.n; m += VT) a += pr.partials[m];
@@ -668,16 +760,8 @@ __device__ __forceinline__ void pre_reduce(const PreReduce& pr) {
     double tot = ws[0];
 #pragma unroll
     for (int w = 1; w < VT / WAVE; ++w) tot += ws[w];
-    const long long q = *pr.qnext;
-    const double r = sqrt(tot);
-    pr.hist[q] = r;
-    const bool bad = !isfinite(r);
-    if (bad || r <= pr.rtol * (*pr.normf)) {
-      *pr.done = 1;
-      *pr.conv_at = q;
-      if (bad) *pr.nonfinite = 1;
-    }
-    *pr.qnext = q + 1;
+    const double one[1] = {tot};
+    *pr.qnext = count_checks<1>(one, q0, pr.hist, normf, pr.rtol, pr.done, pr.conv_at, pr.nonfinite);
   }
 }
 
@@ -686,22 +770,22 @@ __device__ __forceinline__ void pre_reduce(const PreReduce& pr) {
 template <typename T, int BY, int WX, int VAR, unsigned FL>
 __global__ void __launch_bounds__(WAVE * WX * BY)
     k_pass_one(GridArgs g, double* __restrict__ partials, const int* __restrict__ done, PreReduce pr) {
-  if (done != nullptr && *done != 0) return;
+  const int flag = load_flag(done);
   const int nb = (int)gridDim.x - (pr.partials != nullptr ? 1 : 0);  // workgroups taking tiles
   if ((int)blockIdx.x == nb) {
-    pre_reduce(pr);
+    if (!is_set(flag)) pre_reduce(pr);
     return;
   }
   __shared__ Smem<T, BY, WX, VAR> sm;
   const int ntiles = g.tiles_x * g.tiles_y * g.tiles_z;
   if (g.order == 0) {
     for (int t = xcd_remap(blockIdx.x, nb); t < ntiles; t += nb)
-      sweep_tile<T, BY, WX, VAR, FL>(g, t, partials, sm);
+      sweep_tile<T, BY, WX, VAR, FL>(g, t, partials, sm, flag);
   } else {
     const int nv = virtual_tiles(ntiles, g.order, g.chunk);
     for (int vb = blockIdx.x; vb < nv; vb += nb) {
       const int t = g.order == 2 ? xcd_chunked(vb, g.chunk) : vb;
-      if (t < ntiles) sweep_tile<T, BY, WX, VAR, FL>(g, t, partials, sm);
+      if (t < ntiles) sweep_tile<T, BY, WX, VAR, FL>(g, t, partials, sm, flag);
     }
   }
 }
@@ -723,7 +807,7 @@ __global__ void __launch_bounds__(WAVE * WX * BY)
     }
     if (done != nullptr && done[table[lo].id] != 0) continue;
     const GridArgs g = table[lo];
-    sweep_tile<T, BY, WX, VAR, FL>(g, t - g.tile0, partials, sm);
+    sweep_tile<T, BY, WX, VAR, FL>(g, t - g.tile0, partials, sm, 0);
   }
 }
 

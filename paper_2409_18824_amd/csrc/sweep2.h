@@ -77,6 +77,7 @@ __device__ __forceinline__ void sweep2_march(const GridArgs& g, int t, double* _
   T* __restrict__ out = static_cast<T*>(g.o);
   double* __restrict__ u64 = g.u64;
   const T h2 = h2_of<T>(g);
+  [[maybe_unused]] const OverH2 quot(g);  // of the residuals
   const int ztop = g.nz + 1;
 
   int br[RY], cu[RY], cf[RY], co[RY];
@@ -136,7 +137,7 @@ __device__ __forceinline__ void sweep2_march(const GridArgs& g, int t, double* _
       sm.u0edge[(k + 1) & 1][wy][0][lane] = u0p[0];
       sm.u0edge[(k + 1) & 1][wy][1][lane] = u0p[RY - 1];
     }
-    T u1[RY];
+    T u1[RY], sum[RY];
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
       const T nym = r == 0 ? nylo : u0c[r - 1];
@@ -148,11 +149,16 @@ __device__ __forceinline__ void sweep2_march(const GridArgs& g, int t, double* _
       s = s + u0m[r];
       s = s + u0p[r];
       u1[r] = pt_in ? div6(s + h2 * fk[r]) : u0c[r];
-      if (FL & F_RES) {
-        const double res = static_cast<double>(fk[r]) -
-                           (6.0 * static_cast<double>(u0c[r]) - static_cast<double>(s)) / g.h2;
-        acc += (inner[r] && pt_in && k >= k0 && k < k1) ? res * res : 0.0;
-      }
+      sum[r] = s;
+    }
+    if ((FL & F_RES) && k >= k0 && k < k1) {
+      bool act[RY];
+      double res[RY];
+#pragma unroll
+      for (int r = 0; r < RY; ++r) act[r] = inner[r] && col_in[r];
+      quot.residuals(fk, u0c, sum, act, res);
+#pragma unroll
+      for (int r = 0; r < RY; ++r) acc += act[r] ? res[r] * res[r] : 0.0;
     }
     sm.edge[k % 3][wy][0][lane] = u1[0];
     sm.edge[k % 3][wy][1][lane] = u1[RY - 1];

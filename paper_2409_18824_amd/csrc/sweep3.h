@@ -22,8 +22,8 @@
 // single sweep (same neighbour order, no contraction), so the result equals
 // three separate sweeps bit for bit.  The fused residual, when requested, is
 // that of u0 (F_RES, in stage 1), u1 (F_RES1, stage 2) or u2 (F_RES2,
-// stage 3): each stage's neighbour sum is exactly the one the residual of
-// its input needs.  Only the output columns accumulate it, plane by plane
+// stage 3), or all three: each stage's neighbour sum is exactly the one the
+// residual of its input needs.  Only the output columns accumulate it, plane by plane
 // in increasing z whichever the stage.
 #pragma once
 
@@ -44,7 +44,7 @@ struct Smem3 {
   T e0[3][BY][2][WAVE];  // u0: slot, wavefront, first/last row
   T e1[3][BY][2][WAVE];  // u1
   T e2[3][BY][2][WAVE];  // u2
-  double red[BY];
+  double red[3][BY];
 };
 
 // The value of lane l-1 (shl: l+1) of the wavefront; lane 0 (63) gets 0.
@@ -91,10 +91,12 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
   constexpr bool ZERO = (FL & F_FIRST) != 0;
   constexpr uint32_t ES = sizeof(T);
   static_assert(TR >= 5, "a block needs at least one output row");
-  constexpr unsigned RES_ANY = FL & (F_RES | F_RES1 | F_RES2);
+  constexpr unsigned RES_ALL = F_RES | F_RES1 | F_RES2;
+  constexpr unsigned RES_ANY = FL & RES_ALL;
+  constexpr int SETS = RES_ANY == RES_ALL ? 3 : 1;  // fused residuals: one of the three, or all
   static_assert(RES_ANY == 0 || sizeof(T) == 8, "the fused residual is an FP64 pass");
-  static_assert(RES_ANY == 0 || RES_ANY == F_RES || RES_ANY == F_RES1 || RES_ANY == F_RES2,
-                "one fused residual per pass");
+  static_assert(RES_ANY == 0 || RES_ANY == F_RES || RES_ANY == F_RES1 || RES_ANY == F_RES2 || RES_ANY == RES_ALL,
+                "one fused residual per pass, or all three");
   const int lane = threadIdx.x;
   const int wy = __builtin_amdgcn_readfirstlane(threadIdx.y);  // uniform in the wavefront
   const int tx = t % g.tiles_x;
@@ -112,6 +114,7 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
   char* ob = static_cast<char*>(g.o);
   char* u64b = reinterpret_cast<char*>(g.u64);
   const T h2 = h2_of<T>(g);
+  [[maybe_unused]] const OverH2 quot(g);  // of the residuals
   const int ztop = g.nz + 1;
 
   // A wavefront whose rows all lie past the boundary row y = ny + 1 (in a
@@ -125,7 +128,10 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
   if (ty * H - 1 + wy * RY >= g.ny + 2) {
     __syncthreads();
     for (int k = k0 - 2; k <= k1 + 1; ++k) __syncthreads();
-    if (RES_ANY != 0) (void)block_sum<BY>(0.0, sm.red);
+    if (RES_ANY != 0) {
+#pragma unroll
+      for (int i = 0; i < SETS; ++i) (void)block_sum<BY>(0.0, sm.red[i]);
+    }
     __syncthreads();
     return;
   }
@@ -160,7 +166,9 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
   auto u_plane = [&](int kk) { return plane_rsrc(u0b + (uint64_t)(uint32_t)kk * zu); };
   auto f_plane = [&](int kk) { return plane_rsrc(fb + (uint64_t)(uint32_t)kk * zf); };
 
-  double acc = 0.0;
+  double acc[SETS];  // of the residuals in stage order
+#pragma unroll
+  for (int i = 0; i < SETS; ++i) acc[i] = 0.0;
   // Three buffers per plane array, whose roles rotate with k (below,
   // current, above for u0; k-2, k-1, k for u1 and f; k-3, k-2, k-1 for u2):
   // the z loop is unrolled by three, so the rotation is a renaming, not
@@ -229,6 +237,17 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
   }
   __syncthreads();
 
+  bool act[RY];  // output columns
+#pragma unroll
+  for (int r = 0; r < RY; ++r) act[r] = inner3[r] && col_in[r];
+  // the squares of a plane's residuals, of the output columns
+  auto add_residuals = [&](double& a, const T(&fv)[RY], const T(&uv)[RY], const T(&sv)[RY]) {
+    double res[RY];
+    quot.residuals(fv, uv, sv, act, res);
+#pragma unroll
+    for (int r = 0; r < RY; ++r) a += act[r] ? res[r] * res[r] : 0.0;
+  };
+
   // One plane step: u0m/u0c/u0p are u0 at planes k-1, k, k+1, fm2/fm1/fk
   // are f at k-2, k-1, k, u1m2/u1m1/u1 u1 at k-2, k-1, k (u1 computed here)
   // and u2m2/u2m1/u2 u2 at k-3, k-2, k-1 (u2 computed here).
@@ -264,7 +283,7 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
     const bool kout1 = k >= k0 && k < k1;
     // stage 1: u1 at plane k on every row of the block (the quotients by 6
     // in their fused form, then the rare exact divisions, see div6)
-    T x1[RY];
+    T x1[RY], s1[RY];
     uint64_t small1 = 0;  // lanes whose quotient needs the division
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
@@ -279,14 +298,9 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
       x1[r] = s + h2 * fk[r];
       u1[r] = pt_in ? div6_fused(x1[r]) : u0c[r];
       small1 |= __builtin_amdgcn_ballot_w64(pt_in && div6_small(x1[r]));
-      if (FL & F_RES) {
-        if (inner3[r] && pt_in && kout1) {
-          const double res = static_cast<double>(fk[r]) -
-                             (6.0 * static_cast<double>(u0c[r]) - static_cast<double>(s)) / g.h2;
-          acc += res * res;
-        }
-      }
+      s1[r] = s;
     }
+    if ((FL & F_RES) && kout1) add_residuals(acc[0], fk, u0c, s1);
     if (small1 != 0) {
 #pragma unroll
       for (int r = 0; r < RY; ++r)
@@ -301,7 +315,7 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
       const T above = whi ? T(0) : sm.e1[P2][wup][0][lane];
       const bool kin2 = k - 1 >= 1 && k - 1 <= g.nz;
       const bool kout2 = k - 1 >= k0 && k - 1 < k1;
-      T x2[RY];
+      T x2[RY], s2[RY];
       uint64_t small2 = 0;
 #pragma unroll
       for (int r = 0; r < RY; ++r) {
@@ -317,14 +331,9 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
         x2[r] = s + h2 * fm1[r];
         u2[r] = (pt_in && inner2[r]) ? div6_fused(x2[r]) : u1m1[r];
         small2 |= __builtin_amdgcn_ballot_w64(pt_in && inner2[r] && div6_small(x2[r]));
-        if (FL & F_RES1) {
-          if (inner3[r] && pt_in && kout2) {
-            const double res = static_cast<double>(fm1[r]) -
-                               (6.0 * static_cast<double>(u1m1[r]) - static_cast<double>(s)) / g.h2;
-            acc += res * res;
-          }
-        }
+        s2[r] = s;
       }
+      if ((FL & F_RES1) && kout2) add_residuals(acc[SETS == 3 ? 1 : 0], fm1, u1m1, s2);
       if (small2 != 0) {
 #pragma unroll
         for (int r = 0; r < RY; ++r)
@@ -336,9 +345,11 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
     if (k - 2 >= k0) {
       const T below = wlo ? T(0) : sm.e2[P2][wdn][1][lane];
       const T above = whi ? T(0) : sm.e2[P2][wup][0][lane];
+      T s3[RY];
 #pragma unroll
       for (int r = 0; r < RY; ++r) {
         const T xm = shift_in_left(u2m1[r]), xp = shift_in_right(u2m1[r]);
+        s3[r] = T(0);
         if (inner3[r]) {
           const T ym = r == 0 ? below : u2m1[r - 1];
           const T yp = r == RY - 1 ? above : u2m1[r + 1];
@@ -348,15 +359,10 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
           s = s + u2m2[r];
           s = s + u2[r];
           st[r] = div6(s + h2 * fm2[r]);
-          if (FL & F_RES2) {
-            if (col_in[r]) {
-              const double res = static_cast<double>(fm2[r]) -
-                                 (6.0 * static_cast<double>(u2m1[r]) - static_cast<double>(s)) / g.h2;
-              acc += res * res;
-            }
-          }
+          s3[r] = s;
         }
       }
+      if (FL & F_RES2) add_residuals(acc[SETS - 1], fm2, u2m1, s3);
     }
     sm.e2[P][wy][0][lane] = u2[0];
     sm.e2[P][wy][1][lane] = u2[RY - 1];
@@ -373,8 +379,11 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
   flush(k1 - 1);  // the last step computed u3 of plane k1 - 1
 
   if (RES_ANY != 0) {
-    const double tot = block_sum<BY>(acc, sm.red);
-    if (wy == 0 && lane == 0) partials[g.tile0 + t] = tot;
+#pragma unroll
+    for (int i = 0; i < SETS; ++i) {
+      const double tot = block_sum<BY>(acc[i], sm.red[i]);
+      if (wy == 0 && lane == 0) partials[SETS * (g.tile0 + t) + i] = tot;
+    }
   }
   __syncthreads();
 }
@@ -406,6 +415,75 @@ __global__ void __launch_bounds__(WAVE * BY)
       if (t < ntiles) sweep3_tile<T, BY, VAR, FL>(g, t, partials, sm);
     }
   }
+}
+
+// The previous pass's three checks, reduced by one workgroup of T threads
+// (a divisor of 1024) into the same bits as the 1024-thread reduction kernel:
+// thread t stands in for threads t, t + T, t + 2T, ... of that.  All loads of
+// a round of 1024 tiles are in flight together, since the pass ends no sooner
+// than this does.
+template <int T>
+__device__ __forceinline__ void pre_reduce3(const PreReduce& pr) {
+  constexpr int VT = 1024, IT = VT / T;  // threads of the reduction kernel, of those per thread
+  __shared__ double ws[3][VT / WAVE];
+  const int t = threadIdx.y * WAVE + threadIdx.x;
+  const long long q0 = *pr.qnext;  // (on their way together with the partials)
+  const double normf = *pr.normf;
+  double a[IT][3];
+#pragma unroll
+  for (int i = 0; i < IT; ++i) a[i][0] = a[i][1] = a[i][2] = 0.0;
+  for (int m = 0; m < pr.n; m += VT) {
+    double v[IT][3];
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      const int q = m + i * T + t;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) v[i][c] = pr.partials[3LL * min(q, pr.n - 1) + c];
+    }
+#pragma unroll
+    for (int i = 0; i < IT; ++i)
+      if (m + i * T + t < pr.n) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[i][c] += v[i][c];
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < IT; ++i)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const double w = wave_sum(a[i][c]);
+      if (threadIdx.x == 0) ws[c][(i * T + t) / WAVE] = w;
+    }
+  __syncthreads();
+  if (t == 0) {
+    double tot[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      tot[c] = ws[c][0];
+#pragma unroll
+      for (int w = 1; w < VT / WAVE; ++w) tot[c] += ws[c][w];
+    }
+    *pr.qnext = count_checks<3>(tot, q0, pr.hist, normf, pr.rtol, pr.done, pr.conv_at, pr.nonfinite);
+  }
+}
+
+// The three-sweep pass with all three residuals; with pr.partials set, the
+// first workgroup reduces the previous pass's checks instead of taking a tile.
+template <int BY, int VAR>
+__global__ void __launch_bounds__(WAVE * BY)
+    k_sweep3_checks(GridArgs g, double* __restrict__ partials, const int* __restrict__ done, PreReduce pr) {
+  if (done != nullptr && *done != 0) return;
+  const int b0 = pr.partials != nullptr ? 1 : 0;
+  if ((int)blockIdx.x < b0) {
+    pre_reduce3<WAVE * BY>(pr);
+    return;
+  }
+  __shared__ Smem3<double, BY> sm;
+  constexpr unsigned FL = F_WRITE | F_RES | F_RES1 | F_RES2;
+  const int ntiles = g.tiles_x * g.tiles_y * g.tiles_z;
+  const int vb = (int)blockIdx.x - b0;
+  const int t = g.order == 0 ? xcd_remap(vb, (int)gridDim.x - b0) : g.order == 2 ? xcd_chunked(vb, g.chunk) : vb;
+  if (t < ntiles) sweep3_tile<double, BY, VAR, FL>(g, t, partials, sm);
 }
 
 // The three-sweep pass over a table of grids: grid g owns tiles
@@ -507,6 +585,17 @@ hipError_t by_shape3(const TileCfg& c, const GridArgs& g, double* partials, cons
   }
 }
 
+template <int BY, int VAR>
+hipError_t go3_checks(const GridArgs& g, double* partials, const int* done, const PreReduce& pr, hipStream_t st) {
+  const int grid = virtual_tiles(g.tiles_x * g.tiles_y * g.tiles_z, g.order, g.chunk);
+  if (grid <= 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_sweep3_checks<BY, VAR>), dim3(grid + (pr.partials != nullptr ? 1 : 0)), dim3(WAVE, BY), 0,
+                     st, g, partials, done, pr);
+  return hipGetLastError();
+}
+
+hipError_t dispatch_sweep3_checks(const TileCfg& c, const GridArgs& g, double* partials, const int* done,
+                                  const PreReduce& pr, hipStream_t st);
 hipError_t dispatch_sweep3_f64(unsigned flags, const TileCfg& c, const GridArgs& g, double* partials,
                                const int* done, hipStream_t st);
 hipError_t dispatch_sweep3_f32(unsigned flags, const TileCfg& c, const GridArgs& g, double* partials,

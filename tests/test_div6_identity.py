@@ -113,3 +113,35 @@ def test_below_the_cutoff_a_tie_needs_the_division():
     assert x / 6.0 == 2 * 2.0 ** -1074
     assert fused64(x) == 2.0 ** -1074
     assert x < 2.0 ** -1000
+
+
+def over_h2(x: float, h2: float) -> float:
+    """The kernels' division of a residual by h2 = h * h for 2^-900 <= |x| <
+    2^900 and 2^-100 <= h2 <= 2^100 (elsewhere they divide): Markstein's
+    correction of a quotient from 1 / h2 in two parts."""
+    zh = 1.0 / h2
+    zl = float(Fr(float(1 - Fr(h2) * Fr(zh))) * Fr(zh))
+    p = float(Fr(x) * Fr(zh) + Fr(float(Fr(x) * Fr(zl))))
+    rem = Fr(x) - Fr(p) * Fr(h2)
+    assert float(rem) == rem  # the remainder is exact
+    return float(Fr(p) + rem * Fr(zh))
+
+
+def test_residual_quotient_identity():
+    rng = random.Random(63)
+    steps = [1.0 / (n + 1) for n in (1, 5, 64, 100, 511, 512, 1023)] + [0.1, 1e-3, 1.0, 3.0, 2.0 ** 50, 2.0 ** -50,
+                                                                          math.nextafter(1.0, 0.0)]
+    steps += [math.ldexp(rng.getrandbits(52) | (1 << 52), rng.randint(-100, 0)) for _ in range(40)]
+    for h in steps:
+        h2 = h * h
+        if not 2.0 ** -100 <= h2 <= 2.0 ** 100:
+            continue
+        xs = [math.ldexp(rng.getrandbits(52) | (1 << 52), rng.randint(-900, 847)) for _ in range(60)]
+        xs += [2.0 ** -900, math.nextafter(2.0 ** 900, 0.0), 6.0, 1.0, -3.5, math.nextafter(1.0, 0.0)]
+        # dividends next to a representable quotient and next to a tie
+        for _ in range(20):
+            q = math.ldexp(rng.getrandbits(52) | (1 << 52), rng.randint(-60, 0))
+            for v in (Fr(q) * Fr(h2), (Fr(q) + Fr(math.ulp(q)) / 2) * Fr(h2)):
+                xs += [float(v), math.nextafter(float(v), 0.0), -math.nextafter(float(v), math.inf)]
+        for x in xs:
+            assert over_h2(x, h2) == x / h2, (x.hex(), h2.hex())

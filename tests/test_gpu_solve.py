@@ -273,3 +273,33 @@ def test_early_exit_inside_three_sweep_passes(every, rtol):
     assert all(rel(a, b) <= RESID_RTOL for a, b in zip(res.history, ro.history))
     assert rel(res.resid, ro.resid) <= RESID_RTOL
     assert np.array_equal(du.to_numpy(), uo)
+
+
+# more points than the small grids that check in one-sweep passes: every
+# number of sweeps left over, exits at each stage of a pass and in the sweeps
+# left over, replayed chunks (S > 78)
+@pytest.mark.parametrize("S,rtol", [(0, 0.0), (1, 0.0), (2, 0.0), (3, 0.0), (4, 0.0), (8, 0.0), (83, 0.0),
+                                    (84, 2.0), (84, 0.9), (84, 0.6), (84, 0.5), (84, 0.4), (84, 0.05), (5, 0.6),
+                                    (5, 0.5), (5, 0.4), (5, 0.32)])
+def test_checks_after_every_sweep_in_three_sweep_passes(S, rtol, monkeypatch):
+    n = (70, 64, 66)
+    say("three checks per pass", S, rtol)
+    h = 1.0 / 71
+    u0 = synth.uniform_field(*n, 13, 1, 0, 1)
+    f = synth.manufactured_f(*n, h) if rtol == 0.0 else synth.uniform_field(*n, 13, 2, -1, 1)
+    if rtol > 0.0:  # residuals of about 1.9, 0.84, 0.56, 0.43, 0.36, 0.31, ... times the norm of f
+        u0[1:-1, 1:-1, 1:-1] *= 1e-4
+    df = j3d.FArray.from_numpy(f)
+    uo, ro = oracle.solve_plain(u0, f, h, rtol=rtol, check_every=1, max_sweeps=S)
+    for fused in ("1", "0"):
+        monkeypatch.setenv("J3D_SOLVE_FUSED_CHECKS", fused)
+        du = j3d.FArray.from_numpy(u0)
+        res = j3d.poisson_solve(du, df, h, rtol=rtol, max_sweeps=S, check_every=1)
+        assert res.converged == ro.converged and res.sweeps == ro.sweeps, fused
+        assert len(res.history) == len(ro.history)
+        assert all(rel(a, b) <= RESID_RTOL for a, b in zip(res.history, ro.history))
+        assert np.array_equal(du.to_numpy(), uo), fused
+        if fused == "1":
+            first = list(res.history)
+        else:
+            assert first == list(res.history)
