@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from dataclasses import dataclass
 
 import numpy as np
@@ -54,6 +55,10 @@ class J3DArray(ctypes.Structure):
     _fields_ = [("base", ctypes.c_void_p), ("dtype", ctypes.c_int32), ("reserved", ctypes.c_int32),
                 ("lbound", ctypes.c_int64 * 3), ("ubound", ctypes.c_int64 * 3),
                 ("stride", ctypes.c_int64 * 3)]
+
+
+_DESC = struct.Struct("=Qii9q")  # J3DArray's layout
+assert _DESC.size == ctypes.sizeof(J3DArray)
 
 
 class SolveOpts(ctypes.Structure):
@@ -171,6 +176,10 @@ def abi_version() -> int:
 
 def _stream_handle(stream):
     if stream is None:
+        # The raw handle of torch.cuda.current_stream() without its Stream
+        # object: 0.4 us against 3.0, of the 13 a small sweep call took.
+        if torch.cuda.is_initialized():
+            return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
         return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     if isinstance(stream, torch.cuda.Stream):
         return ctypes.c_void_p(stream.cuda_stream)
@@ -230,6 +239,12 @@ class FArray:
         return ex - 2, ey - 2, ez - 2
 
     def desc(self) -> J3DArray:
+        try:  # all fields in one go: half the time of setting them one by one
+            st = self.storage
+            return J3DArray.from_buffer_copy(_DESC.pack(st.data_ptr() + self.offset * st.element_size(), self.dtype, 0,
+                                                        *self.lbound, *self.ubound, *self.stride))
+        except struct.error:
+            pass
         d = J3DArray()
         d.base = self.storage.data_ptr() + self.offset * self.storage.element_size()
         d.dtype = self.dtype
