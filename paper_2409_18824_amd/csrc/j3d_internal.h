@@ -234,12 +234,26 @@ constexpr int kTriadVariants = 3;
 hipError_t launch_triad_variant(int v, const double* a, const double* b, double* dst, long long n,
                                 hipStream_t st);
 // The box of ex x ey x ez doubles at src (row and plane strides ssy, ssz) to
-// dst (dsy, dsz); the boxes may not overlap.
+// dst (dsy, dsz); the boxes may not overlap.  Nothing happens where skip is
+// not null and *skip is set.
 hipError_t launch_copy_box(const double* src, long long ssy, long long ssz, double* dst, long long dsy,
-                           long long dsz, int ex, int ey, int ez, hipStream_t st);
+                           long long dsz, int ex, int ey, int ez, hipStream_t st, const int* skip = nullptr);
 hipError_t launch_copy_interior(const double* src, double* dst, int nx, int ny, int nz,
                                 long long ssy, long long ssz, long long dsy, long long dsz,
-                                hipStream_t st);
+                                hipStream_t st, const int* skip = nullptr);
+
+// The set-up of a solve: the halo of the padded array u (extents ex, ey, ez,
+// strides 1, sy, sz) into a and, where not null, b (u's layout), and a zeroed
+// control block.  The _f32 form: zero halos for count FP32 arrays, one every
+// `apart` bytes from a on.
+hipError_t launch_solve_init(const double* u, double* a, double* b, int ex, int ey, int ez, long long sy,
+                             long long sz, void* ctl, size_t ctl_bytes, hipStream_t st);
+hipError_t launch_solve_init_f32(void* a, int count, size_t apart, int ex, int ey, int ez, long long sy,
+                                 long long sz, void* ctl, size_t ctl_bytes, hipStream_t st);
+// Control words (ctl_bytes, a multiple of 4) and the first n history entries
+// into pinned host memory.
+hipError_t launch_publish(const void* ctl, size_t ctl_bytes, void* host_ctl, const double* hist, int n,
+                          double* host_hist, hipStream_t st);
 hipError_t launch_set_int(int* p, int n, int v, hipStream_t st);
 
 }  // namespace j3d

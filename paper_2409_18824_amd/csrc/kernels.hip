@@ -310,7 +310,8 @@ __global__ void k_triad_tail(const double* __restrict__ a, const double* __restr
 // that short rows cost one access each and not a workgroup.
 __global__ void __launch_bounds__(256)
     k_copy_box(const double* __restrict__ src, long long ssy, long long ssz, double* __restrict__ dst,
-               long long dsy, long long dsz, int ex, int ey, int nrows) {
+               long long dsy, long long dsz, int ex, int ey, int nrows, const int* __restrict__ skip) {
+  if (skip != nullptr && *skip != 0) return;
   const int lane = threadIdx.x & (WAVE - 1);
   for (int row = blockIdx.x * 4 + (int)(threadIdx.x / WAVE); row < nrows; row += gridDim.x * 4) {
     const int k = row / ey, j = row - k * ey;
@@ -318,6 +319,56 @@ __global__ void __launch_bounds__(256)
     double* d = dst + dsy * j + dsz * k;
     for (int i = lane; i < ex; i += WAVE) d[i] = s[i];
   }
+}
+
+// Calls f on the offset of every halo element of a padded array (extents ex,
+// ey, ez, halo included), a wavefront per row: rows on a y or z face whole,
+// the others' two ends.
+template <typename F>
+__device__ __forceinline__ void for_halo(int ex, int ey, int nrows, long long sy, long long sz, F f) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int ez = nrows / ey;
+  for (int row = blockIdx.x * 4 + (int)(threadIdx.x / WAVE); row < nrows; row += gridDim.x * 4) {
+    const int k = row / ey, j = row - k * ey;
+    const bool face = j == 0 || j == ey - 1 || k == 0 || k == ez - 1;
+    const int n = face ? ex : 2;
+    for (int q = lane; q < n; q += WAVE) f(sy * j + sz * k + (face || q == 0 ? q : ex - 1));
+  }
+}
+
+// What a solve sets up, in one launch: the fixed boundary in its other arrays
+// (their interiors are written before they are read) and its control block.
+// A 64^3 solve spent 60 us on copying whole arrays and clearing the block.
+__global__ void __launch_bounds__(256)
+    k_solve_init(const double* __restrict__ u, double* __restrict__ a, double* __restrict__ b, int ex, int ey,
+                 int nrows, long long sy, long long sz, unsigned* ctl, int words) {
+  if (blockIdx.x == 0)
+    for (int q = threadIdx.x; q < words; q += 256) ctl[q] = 0;
+  for_halo(ex, ey, nrows, sy, sz, [&](long long i) {
+    const double v = u[i];
+    a[i] = v;
+    if (b != nullptr) b[i] = v;
+  });
+}
+__global__ void __launch_bounds__(256)
+    k_solve_init_f32(char* a, int count, size_t apart, int ex, int ey, int nrows, long long sy, long long sz,
+                     unsigned* ctl, int words) {
+  if (blockIdx.x == 0)
+    for (int q = threadIdx.x; q < words; q += 256) ctl[q] = 0;
+  for_halo(ex, ey, nrows, sy, sz, [&](long long i) {
+    for (int c = 0; c < count; ++c) reinterpret_cast<float*>(a + c * apart)[i] = 0.0f;
+  });
+}
+
+// The control block and the first n entries of the history into pinned host
+// memory, which a host that waits for the stream then reads (a copy command
+// takes the stream 15 us for each).
+__global__ void __launch_bounds__(256)
+    k_publish(const unsigned* __restrict__ ctl, int words, unsigned* host_ctl, const double* __restrict__ hist, int n,
+              double* host_hist) {
+  for (int q = threadIdx.x; q < words; q += 256) host_ctl[q] = ctl[q];
+  for (int q = threadIdx.x; q < n; q += 256) host_hist[q] = hist[q];
+  __threadfence_system();
 }
 
 __global__ void k_set_int(int* p, int n, int v) {
@@ -619,19 +670,47 @@ hipError_t launch_copy(const double* src, double* dst, long long n, hipStream_t 
 }
 
 hipError_t launch_copy_box(const double* src, long long ssy, long long ssz, double* dst, long long dsy,
-                           long long dsz, int ex, int ey, int ez, hipStream_t st) {
+                           long long dsz, int ex, int ey, int ez, hipStream_t st, const int* skip) {
   const long long nrows = (long long)ey * ez;
   if (ex <= 0 || nrows <= 0) return hipSuccess;
   if (nrows >= (1LL << 31) - 4 * 8192) return hipErrorInvalidValue;
   const int grid = static_cast<int>(min((nrows + 3) / 4, 8192LL));
-  hipLaunchKernelGGL(k_copy_box, dim3(grid), dim3(256), 0, st, src, ssy, ssz, dst, dsy, dsz, ex, ey, (int)nrows);
+  hipLaunchKernelGGL(k_copy_box, dim3(grid), dim3(256), 0, st, src, ssy, ssz, dst, dsy, dsz, ex, ey, (int)nrows,
+                     skip);
   return hipGetLastError();
 }
 
 hipError_t launch_copy_interior(const double* src, double* dst, int nx, int ny, int nz,
                                 long long ssy, long long ssz, long long dsy, long long dsz,
-                                hipStream_t st) {
-  return launch_copy_box(src + (1 + ssy + ssz), ssy, ssz, dst + (1 + dsy + dsz), dsy, dsz, nx, ny, nz, st);
+                                hipStream_t st, const int* skip) {
+  return launch_copy_box(src + (1 + ssy + ssz), ssy, ssz, dst + (1 + dsy + dsz), dsy, dsz, nx, ny, nz, st, skip);
+}
+
+hipError_t launch_solve_init(const double* u, double* a, double* b, int ex, int ey, int ez, long long sy,
+                             long long sz, void* ctl, size_t ctl_bytes, hipStream_t st) {
+  const long long nrows = (long long)ey * ez;
+  if (nrows >= (1LL << 31) - 4 * 8192) return hipErrorInvalidValue;
+  const int grid = static_cast<int>(min((nrows + 3) / 4, 8192LL));
+  hipLaunchKernelGGL(k_solve_init, dim3(grid), dim3(256), 0, st, u, a, b, ex, ey, (int)nrows, sy, sz,
+                     static_cast<unsigned*>(ctl), (int)(ctl_bytes / 4));
+  return hipGetLastError();
+}
+
+hipError_t launch_solve_init_f32(void* a, int count, size_t apart, int ex, int ey, int ez, long long sy,
+                                 long long sz, void* ctl, size_t ctl_bytes, hipStream_t st) {
+  const long long nrows = (long long)ey * ez;
+  if (nrows >= (1LL << 31) - 4 * 8192) return hipErrorInvalidValue;
+  const int grid = static_cast<int>(min((nrows + 3) / 4, 8192LL));
+  hipLaunchKernelGGL(k_solve_init_f32, dim3(grid), dim3(256), 0, st, static_cast<char*>(a), count, apart, ex, ey,
+                     (int)nrows, sy, sz, static_cast<unsigned*>(ctl), (int)(ctl_bytes / 4));
+  return hipGetLastError();
+}
+
+hipError_t launch_publish(const void* ctl, size_t ctl_bytes, void* host_ctl, const double* hist, int n,
+                          double* host_hist, hipStream_t st) {
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(256), 0, st, static_cast<const unsigned*>(ctl), (int)(ctl_bytes / 4),
+                     static_cast<unsigned*>(host_ctl), hist, n, host_hist);
+  return hipGetLastError();
 }
 
 hipError_t launch_set_int(int* p, int n, int v, hipStream_t st) {

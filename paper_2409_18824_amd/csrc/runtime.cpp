@@ -251,7 +251,9 @@ int get_scratch(hipStream_t st, Scratch** out) {
     return rc;
   }
   s->ctl = static_cast<Control*>(p);
-  hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&s->ctl_host), sizeof(Control), hipHostMallocDefault);
+  hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&s->ctl_host), sizeof(Control) + kHostHist * sizeof(double),
+                               hipHostMallocDefault);
+  if (e == hipSuccess) s->hist_host = reinterpret_cast<double*>(s->ctl_host + 1);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&s->ev[0], hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&s->ev[1], hipEventDisableTiming);
   if (e != hipSuccess) {

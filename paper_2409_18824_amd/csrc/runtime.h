@@ -112,6 +112,9 @@ struct Control {
   int nonfinite;
 };
 
+// History entries that reach the host together with the control block.
+constexpr int kHostHist = 4096;
+
 // An instantiated graph of one chunk of a solve, keyed by everything its
 // kernels' arguments depend on.
 struct SolveGraph {
@@ -128,6 +131,7 @@ struct Scratch {
   size_t partials_cap = 0;
   Control* ctl = nullptr;      // device
   Control* ctl_host = nullptr; // pinned host mirror
+  double* hist_host = nullptr; // pinned, kHostHist entries behind ctl_host
   double* hist = nullptr;      // device history
   size_t hist_cap = 0;
   hipEvent_t ev[2] = {nullptr, nullptr};

@@ -43,7 +43,7 @@ int forced_step() {
 }
 
 int publish_done(Scratch* s, int slot, hipStream_t st) {
-  J3D_HIP(hipMemcpyAsync(&s->ctl_host->done, &s->ctl->done, sizeof(int), hipMemcpyDeviceToHost, st));
+  J3D_HIP(launch_publish(&s->ctl->done, sizeof(int), &s->ctl_host->done, nullptr, 0, nullptr, st));
   J3D_HIP(hipEventRecord(s->ev[slot & 1], st));
   return J3D_OK;
 }
@@ -55,17 +55,22 @@ int poll_done(Scratch* s, int slot, bool* done) {
   return J3D_OK;
 }
 
-int read_control(Scratch* s, Control* out, hipStream_t st) {
-  J3D_HIP(hipMemcpyAsync(s->ctl_host, s->ctl, sizeof(Control), hipMemcpyDeviceToHost, st));
+// The control block, and with it the first kHostHist of the nh_max entries of
+// the history there can be.
+int read_control(Scratch* s, long long nh_max, Control* out, hipStream_t st) {
+  J3D_HIP(launch_publish(s->ctl, sizeof(Control), s->ctl_host, s->hist, (int)std::min<long long>(nh_max, kHostHist),
+                         s->hist_host, st));
   J3D_HIP(hipStreamSynchronize(st));
   std::memcpy(out, s->ctl_host, sizeof(Control));
   return J3D_OK;
 }
 
+// After read_control.
 int read_history(Scratch* s, long long nh, std::vector<double>* h, hipStream_t st) {
-  h->assign((size_t)nh, 0.0);
-  if (nh > 0)
-    J3D_HIP(hipMemcpyAsync(h->data(), s->hist, (size_t)nh * sizeof(double), hipMemcpyDeviceToHost, st));
+  h->assign(s->hist_host, s->hist_host + std::min<long long>(nh, kHostHist));
+  if (nh <= kHostHist) return J3D_OK;
+  h->resize((size_t)nh);
+  J3D_HIP(hipMemcpyAsync(h->data(), s->hist, (size_t)nh * sizeof(double), hipMemcpyDeviceToHost, st));
   J3D_HIP(hipStreamSynchronize(st));
   return J3D_OK;
 }
@@ -142,8 +147,6 @@ int solve_fp64_fused_checks(const Field& u, const Field& f, double h, const j3d_
   Field buf3[3] = {u, u, u};
   buf3[1].base = static_cast<char*>(s->work);
   buf3[2].base = static_cast<char*>(s->work) + span;
-  J3D_HIP(hipMemcpyAsync(buf3[1].base, u.base, u.span_bytes(), hipMemcpyDeviceToDevice, st));
-  J3D_HIP(hipMemcpyAsync(buf3[2].base, u.base, u.span_bytes(), hipMemcpyDeviceToDevice, st));
 
   GridArgs one[3], two[3], three[3], resid[3];
   for (int b = 0; b < 3; ++b) {
@@ -159,7 +162,9 @@ int solve_fp64_fused_checks(const Field& u, const Field& f, double h, const j3d_
   J3D_TRY(ensure_partials(s, 2 * ntp));
   double* part[2] = {s->partials, s->partials + ntp};
   J3D_TRY(ensure_hist(s, (size_t)S + 1));
-  J3D_HIP(hipMemsetAsync(s->ctl, 0, sizeof(Control), st));
+  auto dbl = [](const Field& a) { return reinterpret_cast<double*>(a.base); };
+  J3D_HIP(launch_solve_init(dbl(u), dbl(buf3[1]), dbl(buf3[2]), u.ex, u.ey, u.ez, u.sy, u.sz, s->ctl,
+                            sizeof(Control), st));
   J3D_TRY(norm_f(f, cfg, s, st));
   int* done = &s->ctl->done;
   auto pre_of = [&](long long p) {  // the reduction of the checks of pass p
@@ -239,8 +244,13 @@ int solve_fp64_fused_checks(const Field& u, const Field& f, double h, const j3d_
   double* last = part[P & 1];
   J3D_HIP(launch_pass_one_pre(J3D_F64, F_RES, cfg, resid[bl], last, done, pre_of(L == 1 ? P - 1 : -1), st));
   J3D_TRY(count(1, last, nt1));
+  auto to_u = [&](int b, const int* skip) -> int {
+    J3D_HIP(launch_copy_interior(dbl(buf3[b]), dbl(u), u.nx(), u.ny(), u.nz(), u.sy, u.sz, u.sy, u.sz, st, skip));
+    return J3D_OK;
+  };
+  if (bl != 0) J3D_TRY(to_u(bl, done));
   Control ctl;
-  J3D_TRY(read_control(s, &ctl, st));
+  J3D_TRY(read_control(s, S + 1, &ctl, st));
   long long sweeps, nh;
   int at;
   if (ctl.done) {
@@ -256,13 +266,12 @@ int solve_fp64_fused_checks(const Field& u, const Field& f, double h, const j3d_
   } else {
     sweeps = S;
     nh = S + 1;
-    at = bl;
+    at = 0;
   }
   std::vector<double> hist;
   J3D_TRY(read_history(s, nh, &hist, st));
   if (at != 0) {
-    J3D_HIP(launch_copy_interior(reinterpret_cast<const double*>(buf3[at].base), reinterpret_cast<double*>(u.base),
-                                 u.nx(), u.ny(), u.nz(), u.sy, u.sz, u.sy, u.sz, st));
+    J3D_TRY(to_u(at, nullptr));
     J3D_HIP(hipStreamSynchronize(st));
   }
   fill_result(res, sweeps, hist[(size_t)nh - 1], hist, ctl.normf, ctl.done != 0, ctl.nonfinite != 0, o);
@@ -327,12 +336,10 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   const long long period = straight ? std::lcm(c, 3LL) : c;
   const long long period_passes = straight ? period / 3 : step == 3 ? 1 : (lead != 0 ? 1 : 0) + c / step;
 
-  // The second ping-pong array has u's layout and starts as a copy of u
-  // (which gives it the same halo).
+  // the second ping-pong array, of u's layout, with u's halo
   Field w = u;
   J3D_TRY(ensure_work(s, u.span_bytes()));
   w.base = static_cast<char*>(s->work);
-  J3D_HIP(hipMemcpyAsync(w.base, u.base, u.span_bytes(), hipMemcpyDeviceToDevice, st));
 
   const Field* buf[2] = {&u, &w};
   GridArgs one[2], two[2], three[2], resid[2];
@@ -349,7 +356,8 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   const long long nchecks = S / c + 1;
   J3D_TRY(ensure_hist(s, (size_t)nchecks));
 
-  J3D_HIP(hipMemsetAsync(s->ctl, 0, sizeof(Control), st));
+  auto dbl = [](const Field& a) { return reinterpret_cast<double*>(a.base); };
+  J3D_HIP(launch_solve_init(dbl(u), dbl(w), nullptr, u.ex, u.ey, u.ez, u.sy, u.sz, s->ctl, sizeof(Control), st));
   J3D_TRY(norm_f(f, cfg, s, st));
   int* done = &s->ctl->done;
 
@@ -454,8 +462,13 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
       J3D_HIP(launch_reduce_one(s->partials, 0, nt1, &s->ctl->value, nullptr, 0.0, 0, done, nullptr,
                                 nullptr, st));
   }
+  auto to_u = [&](const int* skip) -> int {
+    J3D_HIP(launch_copy_interior(dbl(w), dbl(u), u.nx(), u.ny(), u.nz(), w.sy, w.sz, u.sy, u.sz, st, skip));
+    return J3D_OK;
+  };
+  if (cur == 1) J3D_TRY(to_u(done));
   Control ctl;
-  J3D_TRY(read_control(s, &ctl, st));
+  J3D_TRY(read_control(s, nchecks, &ctl, st));
   long long sweeps, nh;
   int at;
   if (ctl.done) {
@@ -471,14 +484,13 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   } else {
     sweeps = S;
     nh = S / c + 1;
-    at = cur;
+    at = 0;
   }
   std::vector<double> hist;
   J3D_TRY(read_history(s, nh, &hist, st));
   const double resid_v = (ctl.done || S % c == 0) ? hist[(size_t)nh - 1] : ctl.value;
   if (at == 1) {
-    J3D_HIP(launch_copy_interior(reinterpret_cast<const double*>(w.base), reinterpret_cast<double*>(u.base),
-                                 u.nx(), u.ny(), u.nz(), w.sy, w.sz, u.sy, u.sz, st));
+    J3D_TRY(to_u(nullptr));
     J3D_HIP(hipStreamSynchronize(st));
   }
   fill_result(res, sweeps, resid_v, hist, ctl.normf, ctl.done != 0, ctl.nonfinite != 0, o);
@@ -524,7 +536,6 @@ int solve_mixed(const Field& u, const Field& f, double h, const j3d_solve_opts& 
   const Field r32 = f32_field(u, mem, &tmp);
   const Field e0 = f32_field(u, mem + b1, &tmp);
   const Field e1 = f32_field(u, mem + 2 * b1, &tmp);
-  J3D_HIP(hipMemsetAsync(mem, 0, 3 * b1, st));  // zero halos of the correction
 
   // A cycle of m correction sweeps e_1 = J(0), e_{p+1} = J(e_p), u += e_m
   // runs as passes of `step` sweeps: the first pass starts from zero without
@@ -553,7 +564,8 @@ int solve_mixed(const Field& u, const Field& f, double h, const j3d_solve_opts& 
   const long long ncyc = (S + m_in - 1) / m_in + 1;  // defect steps at most
   J3D_TRY(ensure_hist(s, (size_t)ncyc));
 
-  J3D_HIP(hipMemsetAsync(s->ctl, 0, sizeof(Control), st));
+  // zero halos of the correction (and of the residual it is swept with)
+  J3D_HIP(launch_solve_init_f32(r32.base, 3, b1, r32.ex, r32.ey, r32.ez, r32.sy, r32.sz, s->ctl, sizeof(Control), st));
   J3D_TRY(norm_f(f, cd, s, st));
   int* done = &s->ctl->done;
 
@@ -641,7 +653,7 @@ int solve_mixed(const Field& u, const Field& f, double h, const j3d_solve_opts& 
     }
   }
   Control ctl;
-  J3D_TRY(read_control(s, &ctl, st));
+  J3D_TRY(read_control(s, ncyc, &ctl, st));
   long long nh, sweeps;
   if (ctl.done) {
     nh = ctl.conv_at + 1;

@@ -303,3 +303,21 @@ def test_checks_after_every_sweep_in_three_sweep_passes(S, rtol, monkeypatch):
             first = list(res.history)
         else:
             assert first == list(res.history)
+
+
+@pytest.mark.parametrize("S,every", [(4094, 1), (4095, 1), (4096, 1), (9000, 2)])
+def test_long_histories(S, every):
+    """Around the history length that comes back with the control block."""
+    say("long history", S, every)
+    n = (5, 4, 3)
+    u0 = synth.uniform_field(*n, 14, 1, 0, 1)
+    f = synth.uniform_field(*n, 14, 2, -1, 1)
+    du, df = j3d.FArray.from_numpy(u0), j3d.FArray.from_numpy(f)
+    res = j3d.poisson_solve(du, df, 0.1, rtol=0.0, max_sweeps=S, check_every=every)
+    uo, ro = oracle.solve_plain(u0, f, 0.1, rtol=0.0, check_every=every, max_sweeps=S)
+    assert len(res.history) == len(ro.history) == S // every + 1
+    # the first hundred checks; later ones are rounding errors of a converged iterate
+    assert all(rel(a, b) <= RESID_RTOL for a, b in zip(list(res.history)[:100], ro.history[:100]))
+    assert np.all(np.asarray(res.history)[100:] <= np.asarray(ro.history)[100])
+    assert res.resid == res.history[-1]
+    assert np.array_equal(du.to_numpy(), uo)
