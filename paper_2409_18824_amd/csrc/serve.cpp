@@ -144,7 +144,8 @@ struct j3d_server {
   size_t part_cap = 0;
   GridArgs* h_tab = nullptr;  // pinned staging
   double* h_rtol = nullptr;
-  double* h_out = nullptr;    // pinned: resid[max_slots]
+  std::vector<char> uploaded;  // the tables and tolerances on the device
+  double* h_out = nullptr;    // pinned: normf[max_slots], resid[max_slots]
   int* h_flags = nullptr;     // pinned: done[max_slots], nonfinite[max_slots]
   hipEvent_t ev = nullptr;
   TileCfg cd{}, cs{}, cs2{}, cs3{};  // defect, one-, two- and three-sweep FP32 passes
@@ -241,16 +242,16 @@ int setup_device(j3d_server* s) {
   J3D_HIP(hipStreamCreateWithFlags(&s->st, hipStreamNonBlocking));
   J3D_HIP(hipEventCreateWithFlags(&s->ev, hipEventDisableTiming));
   void* p = nullptr;
-  J3D_TRY(dev_alloc(&p, n * sizeof(double), "serve normf")); s->d_normf = (double*)p;
+  J3D_TRY(dev_alloc(&p, 2 * n * sizeof(double), "serve norms")); s->d_normf = (double*)p;
+  s->d_resid = s->d_normf + n;
   J3D_TRY(dev_alloc(&p, n * sizeof(double), "serve rtol")); s->d_rtol = (double*)p;
-  J3D_TRY(dev_alloc(&p, n * sizeof(double), "serve resid")); s->d_resid = (double*)p;
   J3D_TRY(dev_alloc(&p, 2 * n * sizeof(int), "serve flags")); s->d_done = (int*)p;
   s->d_nonfinite = s->d_done + n;
   J3D_TRY(dev_alloc(&p, n * sizeof(long long), "serve conv")); s->d_conv = (long long*)p;
   J3D_TRY(dev_alloc(&p, (size_t)K_NKINDS * n * sizeof(GridArgs), "serve tables")); s->d_tab = (GridArgs*)p;
   J3D_HIP(hipHostMalloc((void**)&s->h_tab, (size_t)K_NKINDS * n * sizeof(GridArgs), hipHostMallocDefault));
   J3D_HIP(hipHostMalloc((void**)&s->h_rtol, n * sizeof(double), hipHostMallocDefault));
-  J3D_HIP(hipHostMalloc((void**)&s->h_out, n * sizeof(double), hipHostMallocDefault));
+  J3D_HIP(hipHostMalloc((void**)&s->h_out, 2 * n * sizeof(double), hipHostMallocDefault));
   J3D_HIP(hipHostMalloc((void**)&s->h_flags, 2 * n * sizeof(int), hipHostMallocDefault));
   J3D_HIP(hipMemsetAsync(s->d_done, 0, 2 * n * sizeof(int), s->st));
   s->cd = TileCfg{1, 16, 20, 0, 2, 1};
@@ -278,7 +279,6 @@ void teardown_device(j3d_server* s) {
   s->active.clear();
   (void)hipFree(s->d_normf);
   (void)hipFree(s->d_rtol);
-  (void)hipFree(s->d_resid);
   (void)hipFree(s->d_done);
   (void)hipFree(s->d_conv);
   (void)hipFree(s->d_tab);
@@ -301,10 +301,11 @@ int queue_setup(j3d_server* s, Slot* sl) {
     // One linear copy of the packed host array into the slot's u and a
     // kernel that spreads its rows over f; u is cleared afterwards.  (A
     // strided copy from the host runs row by row, 8 us each: 12 requests of
-    // 32^3 to 96^3 with f and u on the host took 552 ms, and take 8.9 ms.)
+    // 32^3 to 96^3 with f and u on the host took 552 ms.)  The copy comes
+    // first, so that it does not wait for a fill on another engine.
     double* packed = reinterpret_cast<double*>(sl->L.u.base);
-    J3D_HIP(hipMemsetAsync(sl->mem + sl->L.f_offset, 0, sl->L.bytes - sl->L.f_offset, s->st));
     J3D_HIP(hipMemcpyAsync(packed, q.f.data(), q.f.size() * sizeof(double), hipMemcpyHostToDevice, s->st));
+    J3D_HIP(hipMemsetAsync(sl->mem + sl->L.f_offset, 0, sl->L.bytes - sl->L.f_offset, s->st));
     J3D_HIP(launch_copy_box(packed, f.ex, (long long)f.ex * f.ey, reinterpret_cast<double*>(f.base), f.sy, f.sz,
                             f.ex, f.ey, f.ez, s->st));
     J3D_HIP(hipMemsetAsync(sl->mem, 0, sl->L.f_offset, s->st));
@@ -378,6 +379,33 @@ int admit(j3d_server* s) {
   }
 }
 
+// The tables and tolerances of a cycle to the device, unless they are the last
+// cycle's: steady cycles of a mixed-precision server differ in nothing.
+int upload_tables(j3d_server* s) {
+  const size_t row = (size_t)s->o.max_slots;
+  const size_t tab = (size_t)K_NKINDS * row * sizeof(GridArgs), rtol = row * sizeof(double);
+  std::vector<char>& last = s->uploaded;
+  if (last.size() == tab + rtol && std::memcmp(last.data(), s->h_tab, tab) == 0 &&
+      std::memcmp(last.data() + tab, s->h_rtol, rtol) == 0)
+    return J3D_OK;
+  last.clear();  // (nothing counts as uploaded if a copy fails)
+  J3D_HIP(hipMemcpyAsync(s->d_tab, s->h_tab, tab, hipMemcpyHostToDevice, s->st));
+  J3D_HIP(hipMemcpyAsync(s->d_rtol, s->h_rtol, rtol, hipMemcpyHostToDevice, s->st));
+  const char* t = reinterpret_cast<const char*>(s->h_tab);
+  const char* r = reinterpret_cast<const char*>(s->h_rtol);
+  last.assign(t, t + tab);
+  last.insert(last.end(), r, r + rtol);
+  return J3D_OK;
+}
+
+// Norms, residuals and flags of this cycle's defect step, for the host.
+int finish_cycle(j3d_server* s) {
+  const int row = s->o.max_slots;
+  J3D_HIP(launch_publish(s->d_done, 2 * row * sizeof(int), s->h_flags, s->d_normf, 2 * row, s->h_out, s->st));
+  J3D_HIP(hipEventRecord(s->ev, s->st));
+  return J3D_OK;
+}
+
 // The grids of the slots that still have sweeps left.
 std::vector<Extents> cycle_extents(const std::vector<Slot*>& slots) {
   std::vector<Extents> v;
@@ -443,9 +471,7 @@ int queue_cycle(j3d_server* s, const std::vector<Slot*>& slots) {
     s->part_cap = (size_t)nt_def * 2;
   }
   const size_t row = (size_t)s->o.max_slots;
-  J3D_HIP(hipMemcpyAsync(s->d_tab, s->h_tab, (size_t)K_NKINDS * row * sizeof(GridArgs),
-                         hipMemcpyHostToDevice, s->st));
-  J3D_HIP(hipMemcpyAsync(s->d_rtol, s->h_rtol, row * sizeof(double), hipMemcpyHostToDevice, s->st));
+  J3D_TRY(upload_tables(s));
   GridArgs* D[K_NKINDS];
   for (int k = 0; k < K_NKINDS; ++k) D[k] = s->d_tab + (size_t)k * row;
   int* done = s->d_done;
@@ -477,11 +503,7 @@ int queue_cycle(j3d_server* s, const std::vector<Slot*>& slots) {
       J3D_HIP(pass(step, F_LAST, K_FIRST1, in_e0 ? K_LAST2A : K_LAST2B, in_e0 ? K_LAST3A : K_LAST3B));
     }
   }
-  // Residuals and flags of this cycle's defect step, for the host.
-  J3D_HIP(hipMemcpyAsync(s->h_out, s->d_resid, row * sizeof(double), hipMemcpyDeviceToHost, s->st));
-  J3D_HIP(hipMemcpyAsync(s->h_flags, s->d_done, 2 * row * sizeof(int), hipMemcpyDeviceToHost, s->st));
-  J3D_HIP(hipEventRecord(s->ev, s->st));
-  return J3D_OK;
+  return finish_cycle(s);
 }
 
 // FP64 precision: the residual check of every slot's current iterate, then
@@ -544,9 +566,7 @@ int queue_cycle64(j3d_server* s, const std::vector<Slot*>& slots) {
     s->part_cap = (size_t)nt_def * 2;
   }
   const size_t row = (size_t)s->o.max_slots;
-  J3D_HIP(hipMemcpyAsync(s->d_tab, s->h_tab, (size_t)K_NKINDS * row * sizeof(GridArgs),
-                         hipMemcpyHostToDevice, s->st));
-  J3D_HIP(hipMemcpyAsync(s->d_rtol, s->h_rtol, row * sizeof(double), hipMemcpyHostToDevice, s->st));
+  J3D_TRY(upload_tables(s));
   GridArgs* D[K_NKINDS];
   for (int k = 0; k < K_NKINDS; ++k) D[k] = s->d_tab + (size_t)k * row;
   int* done = s->d_done;
@@ -576,10 +596,7 @@ int queue_cycle64(j3d_server* s, const std::vector<Slot*>& slots) {
       ++s->passes_in_cycle;
     }
   }
-  J3D_HIP(hipMemcpyAsync(s->h_out, s->d_resid, row * sizeof(double), hipMemcpyDeviceToHost, s->st));
-  J3D_HIP(hipMemcpyAsync(s->h_flags, s->d_done, 2 * row * sizeof(int), hipMemcpyDeviceToHost, s->st));
-  J3D_HIP(hipEventRecord(s->ev, s->st));
-  return J3D_OK;
+  return finish_cycle(s);
 }
 
 // Queue the copy of a finished slot's iterate to its host array: its rows
@@ -630,7 +647,6 @@ int retire(j3d_server* s, Slot* sl, bool converged, bool nonfinite, double resid
 
 int worker_loop(j3d_server* s) {
   J3D_TRY(setup_device(s));
-  std::vector<double> normf_h((size_t)s->o.max_slots, 0.0);
   for (;;) {
     J3D_TRY(admit(s));
     if (s->active.empty()) {
@@ -648,7 +664,6 @@ int worker_loop(j3d_server* s) {
     // behind it and they join the next cycle.
     J3D_TRY(admit(s));
     J3D_HIP(hipEventSynchronize(s->ev));
-    J3D_HIP(hipMemcpy(normf_h.data(), s->d_normf, normf_h.size() * sizeof(double), hipMemcpyDeviceToHost));
     std::vector<Slot*> keep, finished;
     const int ms = s->o.max_slots;
     bool copies = false;
@@ -674,7 +689,7 @@ int worker_loop(j3d_server* s) {
       const bool done = s->h_flags[sl->id] != 0, bad = s->h_flags[ms + sl->id] != 0;
       const int id = sl->id;
       s->active.erase(std::find(s->active.begin(), s->active.end(), sl));
-      J3D_TRY(retire(s, sl, done, bad, s->h_out[id], normf_h[id]));
+      J3D_TRY(retire(s, sl, done, bad, s->h_out[ms + id], s->h_out[id]));
     }
     bool stop;
     {
