@@ -933,6 +933,15 @@ int autotune_batch3_fields(const BatchFields& bf, const TileCfg& c, bool pairs, 
       cand3.push_back(k);
       cand3.push_back(TileCfg{k.rows, k.planes, k.variant, k.persistent, kOrderSlots, k.cols});
     }
+    // batches too small to fill the chip with tiles of 16 planes (60 sweeps of
+    // 4 grids of 32^3 to 40^3: 256 us against 320; 8 of 32^3 to 96^3: 605
+    // against 707)
+    std::vector<Extents> ext;
+    for (const Field& a : bf.a) ext.push_back(Extents{a.nx(), a.ny(), a.nz()});
+    TileCfg k = modelled_shape(3, J3D_F64, ext.data(), n);
+    cand3.push_back(k);
+    k.order = kOrderSlots;
+    cand3.push_back(k);
   }
   rc = time_list(st, best3, cand3, launch3, &t3);
   TileCfg other = pairs ? c2 : c;
@@ -945,6 +954,19 @@ int autotune_batch3_fields(const BatchFields& bf, const TileCfg& c, bool pairs, 
   if (dslots) (void)hipFree(dslots);
   *use = t3 / 3.f < tother / (pairs ? 2.f : 1.f);
   return rc;
+}
+
+// Two- and three-sweep shapes where a batch has none of its own (an explicit
+// shape that those kernels do not have): 4 wavefronts, 16 planes, or what is
+// tuned for 64^3.
+TileCfg batch_default(int sweeps) {
+  TileCfg c;
+  if (sweeps == 2) {
+    if (tune_cache_lookup_single(J3D_KIND_F64X2, 64, 64, 64, &c) && tile2_cfg_supported(J3D_F64, c)) return c;
+    return TileCfg{4, 16, 20, 0, 1, 1};
+  }
+  if (tune_cache_lookup_single(J3D_KIND_F64X3, 64, 64, 64, &c) && tile3_cfg_supported(J3D_F64, c)) return c;
+  return TileCfg{4, 16, 6, 0, 0, 1};
 }
 
 }  // namespace j3d
@@ -980,7 +1002,7 @@ extern "C" int jacobi3d_sweep_batch(int32_t ngrids, j3d_grid* grids, int32_t nsw
   // the two-sweep kernel has it (else the default two-sweep shape), so that
   // a grid's numbers do not depend on the batch it is in.
   bool pairs = false;
-  TileCfg c2 = default_cfg2(J3D_F64, 64, 64, 64);
+  TileCfg c2 = batch_default(2);
   if (tune != nullptr && tile2_cfg_supported(J3D_F64, c)) c2 = c;
   const char* force = getenv("J3D_BATCH_PAIRS");
   const int mode = (force && *force == '0') ? 0 : (force && *force == '1') ? 1 : -1;
@@ -1005,7 +1027,7 @@ extern "C" int jacobi3d_sweep_batch(int32_t ngrids, j3d_grid* grids, int32_t nsw
   // regardless of timing; an explicit tile shape is used for the
   // three-sweep passes when that kernel has it.
   bool triples = false;
-  TileCfg c3 = default_cfg3(J3D_F64, 64, 64, 64);
+  TileCfg c3 = batch_default(3);
   bool keep_c3 = false;
   if (tune != nullptr && tile3_cfg_supported(J3D_F64, c)) {
     c3 = c;
