@@ -182,13 +182,16 @@ TileCfg default_cfg2(int dtype, int nx, int ny, int nz) {
   const Extents e{nx, ny, nz};
   const long long pts = (long long)nx * ny * nz;
   if (modelled_size(pts)) return modelled_shape(2, dtype, &e, 1);
-  // up to 400^3 (measured at 256^3): 4 wavefronts of 4 rows, XCD-blocked, 32
-  // planes in FP64 (86 us against 106 with the shape below), 16 in FP32 (42
-  // against 58)
-  if (pts >= 4096 && pts <= 400LL * 400 * 400) return TileCfg{4, dtype == J3D_F32 ? 16 : 32, 20, 0, 0, 1};
-  // measured at 512^3: FP64 16 rows per block, 16 planes, launch order;
-  // FP32 32 rows per block, 8 planes, XCD-blocked order (4 rows per thread,
-  // nontemporal stores in both)
+  // FP32 up to 400^3 (measured at 256^3): 4 wavefronts of 4 rows, XCD-blocked,
+  // 16 planes (42 us against 58 with the shape below)
+  if (dtype == J3D_F32 && pts >= 4096 && pts <= 400LL * 400 * 400) return TileCfg{4, 16, 20, 0, 0, 1};
+  // FP64: 4 wavefronts of 4 rows, 12 planes, per-slab XCD chunks (us per pass,
+  // in brackets with 16 planes in launch order: 256^3 92 [103], 300^3 140
+  // [156], 200x300x500 167 [181], 400^3 331 [336], 512^3 672 [690])
+  if (dtype == J3D_F64 && pts >= (1LL << 24)) return TileCfg{4, 12, 20, 0, 2, 1};
+  // FP32 measured at 512^3: 32 rows per block, 8 planes, XCD-blocked order (4
+  // rows per thread, nontemporal stores); small grids are one latency in any
+  // shape
   c.rows = dtype == J3D_F32 ? 8 : 4;
   c.planes = dtype == J3D_F32 ? 8 : 16;
   c.variant = 20;

@@ -115,6 +115,30 @@ __device__ __forceinline__ double from_right(double v) {
   return __builtin_bit_cast(double, r);
 }
 
+// The value of lane l-1 (shl: l+1) of the wavefront; lane 0 (63) gets 0.
+// One DPP move per 32-bit half, with no copy of the destination first: the
+// multi-sweep tiles never use the shifted value at their edge lanes.
+__device__ __forceinline__ double shift_in_left(double v) {
+  const dpp_i2 a = __builtin_bit_cast(dpp_i2, v);
+  dpp_i2 r;
+  r.x = __builtin_amdgcn_mov_dpp(a.x, 0x138, 0xF, 0xF, true);
+  r.y = __builtin_amdgcn_mov_dpp(a.y, 0x138, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, r);
+}
+__device__ __forceinline__ double shift_in_right(double v) {
+  const dpp_i2 a = __builtin_bit_cast(dpp_i2, v);
+  dpp_i2 r;
+  r.x = __builtin_amdgcn_mov_dpp(a.x, 0x130, 0xF, 0xF, true);
+  r.y = __builtin_amdgcn_mov_dpp(a.y, 0x130, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, r);
+}
+__device__ __forceinline__ float shift_in_left(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x138, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float shift_in_right(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x130, 0xF, 0xF, true));
+}
+
 // The value lane `src` (a constant) of the wavefront holds, in every lane.
 __device__ __forceinline__ float lane_value(float v, int src) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));

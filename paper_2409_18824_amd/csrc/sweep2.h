@@ -26,6 +26,12 @@
 // single sweep (same neighbour order, no contraction), so the result equals
 // two separate sweeps bit for bit.  The fused residual, when requested, is
 // that of u0 (the input), accumulated by the output columns only.
+//
+// Bound by latency on small grids and by memory from about 300^3 on.  The
+// loads of a step are issued a step ahead and its results stored a step
+// later, behind the next loads; us per pass with them, in brackets without:
+// FP64 64^3 7.3 [7.9], 128^3 16.1 [17.8], 333x222x111 40.2 [42.6], 512^3 672
+// [700]; FP32 64^3 6.2 [6.6], 256^3 42.2 [44.1], 512^3 400 [412].
 #pragma once
 
 #include "sweep.h"
@@ -60,7 +66,7 @@ __device__ __forceinline__ void sweep2_march(const GridArgs& g, int t, double* _
   static_assert(TR >= 3, "a block needs at least one inner row");
   static_assert(!(FL & F_RES) || sizeof(T) == 8, "the fused residual is an FP64 pass");
   const int lane = threadIdx.x;
-  const int wy = threadIdx.y;
+  const int wy = __builtin_amdgcn_readfirstlane(threadIdx.y);  // uniform in the wavefront
   const int tx = t % g.tiles_x;
   const int t2 = t / g.tiles_x;
   const int ty = t2 % g.tiles_y;
@@ -109,6 +115,47 @@ __device__ __forceinline__ void sweep2_march(const GridArgs& g, int t, double* _
     u1m2[r] = T(0);
     fprev[r] = T(0);
   }
+  // The loads a step consumes (u0 one plane above, f at its plane, and the
+  // outer wavefronts' u0 rows beyond the block) are issued at the start of the
+  // step before, so that a step of arithmetic covers their latency.
+  const bool wlo = wy == 0, whi = wy == BY - 1;
+  T pu[RY], pf[RY], plo = T(0), phi = T(0);
+  auto issue = [&](int k) {
+    const int kp = min(k + 1, ztop);
+    const int kf = min(max(k, 1), g.nz);
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      pf[r] = f[cf[r] + g.sf_z * kf];
+      pu[r] = ZERO ? T(0) : u0[cu[r] + g.su_z * kp];
+    }
+    if (!ZERO) {
+      const int zk = g.su_z * min(k, ztop);
+      plo = wlo ? u0[cym + zk] : T(0);
+      phi = whi ? u0[cyp + zk] : T(0);
+    }
+  };
+  // u2 of the plane a step computed is stored at the start of the next one,
+  // behind that one's loads, whose wait then covers no store; with F_LAST, pq
+  // holds the FP64 values it is added to.
+  T st[RY];
+  double pq[RY];
+#pragma unroll
+  for (int r = 0; r < RY; ++r) {
+    st[r] = T(0);
+    pq[r] = 0.0;
+  }
+  auto flush = [&](int k) {
+#pragma unroll
+    for (int r = 0; r < RY; ++r) {
+      if (inner[r] && col_in[r]) {
+        if (FL & F_LAST)
+          u64[co[r] + g.s64_z * k] = pq[r] + static_cast<double>(st[r]);
+        else
+          put<T, NT>(out + co[r] + g.so_z * k, st[r]);
+      }
+    }
+  };
+  issue(k0 - 1);
   // The u0 rows just below and above a wavefront's rows are the neighbouring
   // wavefronts' edge rows: they pass through LDS (two plane slots), and only
   // the block's outer wavefronts load the rows beyond the block.
@@ -118,38 +165,55 @@ __device__ __forceinline__ void sweep2_march(const GridArgs& g, int t, double* _
     __syncthreads();
   }
 
+  const int wdn = max(wy - 1, 0), wup = min(wy + 1, BY - 1);  // neighbouring wavefronts
   for (int k = k0 - 1; k <= k1; ++k) {
-    // Stage 1: u1 at plane k on every row of the block.
-    const int kp = min(k + 1, ztop);
-    const int kf = min(max(k, 1), g.nz);
-    const int zk = g.su_z * k;
+    // Stage 1: u1 at plane k on every row of the block (the quotients by 6 in
+    // their fused form, then the rare exact divisions, see div6).
     T u0p[RY], fk[RY];
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
-      fk[r] = f[cf[r] + g.sf_z * kf];
-      u0p[r] = ZERO ? T(0) : u0[cu[r] + g.su_z * kp];
+      fk[r] = pf[r];
+      u0p[r] = pu[r];
+    }
+    const T elo = plo, ehi = phi;
+    if (k < k1) issue(k + 1);
+    if (k - 2 >= k0) flush(k - 2);
+    if ((FL & F_LAST) && k - 1 >= k0) {
+#pragma unroll
+      for (int r = 0; r < RY; ++r)
+        if (inner[r] && col_in[r]) pq[r] = u64[co[r] + g.s64_z * (k - 1)];
     }
     T nylo = T(0), nyhi = T(0);
     if (!ZERO) {
-      nylo = wy > 0 ? sm.u0edge[k & 1][wy - 1][1][lane] : u0[cym + zk];
-      nyhi = wy < BY - 1 ? sm.u0edge[k & 1][wy + 1][0][lane] : u0[cyp + zk];
+      const T dn = sm.u0edge[k & 1][wdn][1][lane], up = sm.u0edge[k & 1][wup][0][lane];
+      nylo = wlo ? elo : dn;
+      nyhi = whi ? ehi : up;
       // plane k+1 for the next step (read after this step's barrier)
       sm.u0edge[(k + 1) & 1][wy][0][lane] = u0p[0];
       sm.u0edge[(k + 1) & 1][wy][1][lane] = u0p[RY - 1];
     }
-    T u1[RY], sum[RY];
+    const bool kin = k >= 1 && k <= g.nz;
+    T u1[RY], x1[RY], sum[RY];
+    uint64_t small = 0;  // lanes whose quotient needs the division
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
       const T nym = r == 0 ? nylo : u0c[r - 1];
       const T nyp = r == RY - 1 ? nyhi : u0c[r + 1];
-      const bool pt_in = col_in[r] && k >= 1 && k <= g.nz;
-      T s = ZERO ? T(0) : from_left(u0c[r]) + from_right(u0c[r]);
+      const bool pt_in = col_in[r] && kin;
+      T s = ZERO ? T(0) : shift_in_left(u0c[r]) + shift_in_right(u0c[r]);
       s = s + nym;
       s = s + nyp;
       s = s + u0m[r];
       s = s + u0p[r];
-      u1[r] = pt_in ? div6(s + h2 * fk[r]) : u0c[r];
       sum[r] = s;
+      x1[r] = s + h2 * fk[r];
+      u1[r] = pt_in ? div6_fused(x1[r]) : u0c[r];
+      small |= __builtin_amdgcn_ballot_w64(pt_in && div6_small(x1[r]));
+    }
+    if (small != 0) {
+#pragma unroll
+      for (int r = 0; r < RY; ++r)
+        if (col_in[r] && kin && div6_small(x1[r])) u1[r] = x1[r] / T(6);
     }
     if ((FL & F_RES) && k >= k0 && k < k1) {
       bool act[RY];
@@ -166,30 +230,27 @@ __device__ __forceinline__ void sweep2_march(const GridArgs& g, int t, double* _
     // Stage 2: u2 at plane k-1 on the output columns.
     if (k - 1 >= k0) {
       const int sl = (k + 2) % 3;  // slot of plane k-1
-      const T above = wy > 0 ? sm.edge[sl][wy - 1][1][lane] : T(0);
-      const T below = wy < BY - 1 ? sm.edge[sl][wy + 1][0][lane] : T(0);
+      const T above = sm.edge[sl][wdn][1][lane];  // (not used past the block's rows)
+      const T below = sm.edge[sl][wup][0][lane];
+      T x2[RY];
+      small = 0;
 #pragma unroll
       for (int r = 0; r < RY; ++r) {
-        const T xm = from_left(u1m1[r]);
-        const T xp = from_right(u1m1[r]);
-        if (inner[r]) {
-          const T ym = r == 0 ? above : u1m1[r - 1];
-          const T yp = r == RY - 1 ? below : u1m1[r + 1];
-          T s1 = xm + xp;
-          s1 = s1 + ym;
-          s1 = s1 + yp;
-          s1 = s1 + u1m2[r];
-          s1 = s1 + u1[r];
-          const T u2 = div6(s1 + h2 * fprev[r]);
-          if (col_in[r]) {
-            if (FL & F_LAST) {
-              double* q = u64 + co[r] + g.s64_z * (k - 1);
-              q[0] = q[0] + static_cast<double>(u2);
-            } else {
-              put<T, NT>(out + co[r] + g.so_z * (k - 1), u2);
-            }
-          }
-        }
+        const T ym = r == 0 ? above : u1m1[r - 1];
+        const T yp = r == RY - 1 ? below : u1m1[r + 1];
+        T s = shift_in_left(u1m1[r]) + shift_in_right(u1m1[r]);
+        s = s + ym;
+        s = s + yp;
+        s = s + u1m2[r];
+        s = s + u1[r];
+        x2[r] = s + h2 * fprev[r];
+        st[r] = div6_fused(x2[r]);
+        small |= __builtin_amdgcn_ballot_w64(inner[r] && col_in[r] && div6_small(x2[r]));
+      }
+      if (small != 0) {
+#pragma unroll
+        for (int r = 0; r < RY; ++r)
+          if (inner[r] && col_in[r] && div6_small(x2[r])) st[r] = x2[r] / T(6);
       }
     }
 #pragma unroll
@@ -201,6 +262,7 @@ __device__ __forceinline__ void sweep2_march(const GridArgs& g, int t, double* _
       fprev[r] = fk[r];
     }
   }
+  flush(k1 - 1);  // the last step computed u2 of plane k1 - 1
 
   if (FL & F_RES) {
     const double tot = block_sum<BY * WX>(acc, sm.red);
@@ -219,8 +281,16 @@ __device__ __forceinline__ void sweep2_tile(const GridArgs& g, int t, double* __
     sweep2_march<T, BY, WX, VAR, FL>(g, t, partials, sm);
 }
 
+// Wavefronts per SIMD that the registers have to leave room for: FP32 with
+// four rows per thread fits 80 registers instead of 83 and with them a sixth
+// wavefront (256^3 42.2 us against 45.4); FP64 gains nothing from a bound.
+template <typename T>
+constexpr int waves2(int var) {
+  return sizeof(T) == 4 && rows_per_thread(var) == 4 ? 6 : 1;
+}
+
 template <typename T, int BY, int WX, int VAR, unsigned FL>
-__global__ void __launch_bounds__(WAVE * WX * BY)
+__global__ void __launch_bounds__(WAVE * WX * BY, waves2<T>(VAR))
     k_sweep2_one(GridArgs g, double* __restrict__ partials, const int* __restrict__ done) {
   if (done != nullptr && *done != 0) return;
   __shared__ Smem2<T, BY, WX> sm;
@@ -239,7 +309,7 @@ __global__ void __launch_bounds__(WAVE * WX * BY)
 
 // The two-sweep pass over a table of grids (as k_pass_batch).
 template <typename T, int BY, int WX, int VAR, unsigned FL>
-__global__ void __launch_bounds__(WAVE * WX * BY)
+__global__ void __launch_bounds__(WAVE * WX * BY, waves2<T>(VAR))
     k_sweep2_batch(const GridArgs* __restrict__ table, int ngrids, int ntiles,
                    double* __restrict__ partials, const int* __restrict__ done, int order, int chunk) {
   __shared__ Smem2<T, BY, WX> sm;

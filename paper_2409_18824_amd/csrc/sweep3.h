@@ -47,30 +47,6 @@ struct Smem3 {
   double red[3][BY];
 };
 
-// The value of lane l-1 (shl: l+1) of the wavefront; lane 0 (63) gets 0.
-// One DPP move per 32-bit half, with no copy of the destination first: the
-// three-sweep tile never uses the shifted value at its edge lanes.
-__device__ __forceinline__ double shift_in_left(double v) {
-  const dpp_i2 a = __builtin_bit_cast(dpp_i2, v);
-  dpp_i2 r;
-  r.x = __builtin_amdgcn_mov_dpp(a.x, 0x138, 0xF, 0xF, true);
-  r.y = __builtin_amdgcn_mov_dpp(a.y, 0x138, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, r);
-}
-__device__ __forceinline__ double shift_in_right(double v) {
-  const dpp_i2 a = __builtin_bit_cast(dpp_i2, v);
-  dpp_i2 r;
-  r.x = __builtin_amdgcn_mov_dpp(a.x, 0x130, 0xF, 0xF, true);
-  r.y = __builtin_amdgcn_mov_dpp(a.y, 0x130, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, r);
-}
-__device__ __forceinline__ float shift_in_left(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x138, 0xF, 0xF, true));
-}
-__device__ __forceinline__ float shift_in_right(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x130, 0xF, 0xF, true));
-}
-
 // Flags as for the two-sweep pass: F_WRITE (store u3 to g.o), F_RES (FP64:
 // residual of u0; F_RES1, F_RES2: of u1, u2), F_FIRST (u0 is identically
 // zero and not read), F_LAST (add (double) u3 to g.u64 instead of storing
