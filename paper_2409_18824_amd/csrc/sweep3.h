@@ -218,10 +218,18 @@ __device__ __forceinline__ void sweep3_march(const GridArgs& g, int t, double* _
   for (int r = 0; r < RY; ++r) act[r] = inner3[r] && col_in[r];
   // the squares of a plane's residuals, of the output columns
   auto add_residuals = [&](double& a, const T(&fv)[RY], const T(&uv)[RY], const T(&sv)[RY]) {
-    double res[RY];
-    quot.residuals(fv, uv, sv, act, res);
+    // by pairs of rows: the block's ring is two rows deep, so a pair is output
+    // rows or none
 #pragma unroll
-    for (int r = 0; r < RY; ++r) a += act[r] ? res[r] * res[r] : 0.0;
+    for (int p = 0; p < RY; p += 2) {
+      if (wy * RY + p < 2 || wy * RY + p >= TR - 2) continue;  // uniform
+      const T f2[2] = {fv[p], fv[p + 1]}, u2[2] = {uv[p], uv[p + 1]}, s2[2] = {sv[p], sv[p + 1]};
+      const bool act2[2] = {act[p], act[p + 1]};
+      double res[2];
+      quot.residuals(f2, u2, s2, act2, res);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) a += act2[r] ? res[r] * res[r] : 0.0;
+    }
   };
 
   // One plane step: u0m/u0c/u0p are u0 at planes k-1, k, k+1, fm2/fm1/fk
@@ -375,8 +383,17 @@ __device__ __forceinline__ void sweep3_tile(const GridArgs& g, int t, double* __
     sweep3_march<T, BY, VAR, FL>(g, t, partials, sm);
 }
 
+// Wavefronts per SIMD that the registers have to leave room for: FP64 with
+// four rows per thread keeps three with the residual of the input or of u1
+// (168 registers instead of 170 and 178: 256^3 124 and 127 us per pass instead
+// of 140 and 140); that of u2 would spill (186 us instead of 137).
+template <typename T>
+constexpr int waves3(int by, int var, unsigned fl) {
+  return sizeof(T) == 8 && by <= 4 && rows_per_thread(var) == 4 && (fl & F_RES2) == 0 ? 3 : 1;
+}
+
 template <typename T, int BY, int VAR, unsigned FL>
-__global__ void __launch_bounds__(WAVE * BY)
+__global__ void __launch_bounds__(WAVE * BY, waves3<T>(BY, VAR, FL))
     k_sweep3_one(GridArgs g, double* __restrict__ partials, const int* __restrict__ done) {
   if (done != nullptr && *done != 0) return;
   __shared__ Smem3<T, BY> sm;
@@ -466,7 +483,7 @@ __global__ void __launch_bounds__(WAVE * BY)
 // [table[g].tile0, table[g].tile0 + tiles(g)) of one flat list (found by
 // binary search over tile0), as the two-sweep batched pass.
 template <typename T, int BY, int VAR, unsigned FL>
-__global__ void __launch_bounds__(WAVE * BY)
+__global__ void __launch_bounds__(WAVE * BY, waves3<T>(BY, VAR, FL))
     k_sweep3_batch(const GridArgs* __restrict__ table, int ngrids, int ntiles, double* __restrict__ partials,
                    const int* __restrict__ done, int order, int chunk, const TileSlot* __restrict__ slots) {
   __shared__ Smem3<T, BY> sm;
