@@ -136,41 +136,56 @@ TileCfg default_cfg3(int dtype, int nx, int ny, int nz) {
     // allocation-free entry point's fixed number of partials must hold)
     if ((long long)tx * ty * tz <= 65536) return c;
   }
-  // measured on cubes from 96^3 to 512^3 (nontemporal stores throughout):
-  // up to about 200^3 points 4 wavefronts of 2 rows per thread and 16
-  // planes (more, thinner tiles), XCD-blocked; up to about 300^3, 4
-  // wavefronts of 4 rows per thread, per-slab XCD chunks; beyond, 8
-  // wavefronts of 2 rows per thread (about 95 registers per thread against
-  // 160 with 4 rows, so twice the wavefronts per CU), 32 planes in
-  // per-slab XCD chunks.  Above 400^3 (measured at 512^3): FP64 16
-  // wavefronts of 2 rows (32-row blocks, one workgroup per CU) and 144
-  // planes in launch order, 712 us per pass against 731 with 8 wavefronts
-  // and 96 planes (the block's waste on ragged y edges is small since
-  // wavefronts wholly past the grid skip their work; 144 planes make four
-  // z-slabs, the last one short); FP32 8 wavefronts of 2 rows, 48 planes,
-  // per-slab XCD chunks, 419 us against 439 with 4 wavefronts of 4 rows and
-  // 24 planes.  Other sizes above 400^3 are best tuned (j3d_autotune_single).
   const long long pts = (long long)nx * ny * nz;
+  // FP32 from 2^24 points while all tiles are resident at once (five
+  // workgroups per CU): 4 wavefronts of 4 rows, 24 planes, XCD-blocked (us per
+  // pass, in brackets per-slab XCD chunks of 16 planes; tiles: 256^3 51.5
+  // [57.5] 1210, 256x200x330 51.5 [58.5], 264^3 56.4 [59.8] 1210; 280x300x260
+  // 80 [69] 1375, 270x280x280 73 [65] 1440).
+  if (dtype == J3D_F32 && pts >= (1LL << 24) && pts <= 300LL * 300 * 300) {
+    c = TileCfg{4, 24, 20, 0, 0, 1};
+    int tx, ty, tz;
+    tile3_counts(nx, ny, nz, c, &tx, &ty, &tz);
+    if ((long long)tx * ty * tz <= 5 * 256) return c;
+  }
+  // FP64 above 400^3: 16 wavefronts of 2 rows (32-row blocks, one workgroup
+  // per CU), 144 planes in launch order (512^3 712 us per pass against 731
+  // with 8 wavefronts and 96 planes).  One workgroup lasts a whole round of
+  // the CUs, so where the last of a few rounds is less than half full, 32
+  // planes in per-slab XCD chunks (us per pass, in brackets 144 planes; rounds):
+  // 420^3 428 [490] 1.4, 460^3 518 [559] 2.1, 512x512x300 434 [510] 2.0,
+  // 600x500x400 658 [725] 2.3, 800x400x300 528 [538] 2.5, 560x540x520 842 [960]
+  // 3.1; but 500^3 678 [694] and with a residual 721 [713] 2.5, 512^3 720 [718]
+  // and 764 [753] 2.7.
+  if (dtype == J3D_F64 && pts > 400LL * 400 * 400) {
+    c = TileCfg{16, 144, 6, 0, 1, 1};
+    int tx, ty, tz;
+    tile3_counts(nx, ny, nz, c, &tx, &ty, &tz);
+    const long long tiles = (long long)tx * ty * tz, last = tiles % 256;
+    if (tiles < 4 * 256 && last > 0 && last < 128) {
+      const TileCfg s{16, 32, 6, 0, 2, 1};
+      tile3_counts(nx, ny, nz, s, &tx, &ty, &tz);
+      if ((long long)tx * ty * tz <= 65536) c = s;
+    }
+    return c;
+  }
+  // Otherwise, up to 2^24 points (FP32 300^3), 4 wavefronts of 4 rows per
+  // thread, 16 planes in per-slab XCD chunks; beyond, 8 wavefronts of 2 rows
+  // per thread (about 95 registers per thread against 160 with 4 rows, so
+  // twice the wavefronts per CU), 32 planes (FP64 300x320x280 165 us against
+  // 177 with 4 x 4 rows, 280x300x260 121; at 256^3, whose default is older, 109
+  // against 115); FP32 above 400^3 48 planes
+  // (512^3 419 us against 439 with 4 wavefronts of 4 rows and 24 planes).
+  // Below 200^3 points only grids too flat for the model come here: 4
+  // wavefronts of 2 rows, XCD-blocked.
   const bool small = pts <= 200LL * 200 * 200;
-  const bool large = pts > 300LL * 300 * 300;
-  const bool huge = pts > 400LL * 400 * 400;
+  const bool large = pts > (dtype == J3D_F32 ? 300LL * 300 * 300 : 1LL << 24);
   c.rows = large ? 8 : 4;
-  c.planes = large ? 32 : 16;
+  c.planes = !large ? 16 : dtype == J3D_F32 && pts > 400LL * 400 * 400 ? 48 : 32;
   c.variant = (small || large) ? 6 : 20;
   c.persistent = 0;
   c.order = small ? 0 : 2;
   c.cols = 1;
-  if (huge) {
-    if (dtype == J3D_F32) {
-      c.rows = 8;
-      c.planes = 48;
-      c.order = 2;
-    } else {
-      c.rows = 16;
-      c.planes = 144;
-      c.order = 1;
-    }
-  }
   return c;
 }
 
@@ -182,16 +197,19 @@ TileCfg default_cfg2(int dtype, int nx, int ny, int nz) {
   const Extents e{nx, ny, nz};
   const long long pts = (long long)nx * ny * nz;
   if (modelled_size(pts)) return modelled_shape(2, dtype, &e, 1);
-  // FP32 up to 400^3 (measured at 256^3): 4 wavefronts of 4 rows, XCD-blocked,
-  // 16 planes (42 us against 58 with the shape below)
-  if (dtype == J3D_F32 && pts >= 4096 && pts <= 400LL * 400 * 400) return TileCfg{4, 16, 20, 0, 0, 1};
+  // FP32 up to 300^3: 4 wavefronts of 4 rows, 8 planes, XCD-blocked; beyond,
+  // where the halo rows of a contiguous block overflow an XCD's L2, 8
+  // wavefronts of 2 rows, 12 planes in per-slab XCD chunks (us per pass,
+  // first / second: 256^3 40.5 / 45.5, 300x320x280 73.4 / 72.6, 512x300x200
+  // 93 / 86, 400^3 207 / 188, 460^3 330 / 275, 512^3 405 / 374, 700x640x600
+  // 927 / 749).
+  if (dtype == J3D_F32 && pts >= 4096)
+    return pts <= 300LL * 300 * 300 ? TileCfg{4, 8, 20, 0, 0, 1} : TileCfg{8, 12, 6, 0, 2, 1};
   // FP64: 4 wavefronts of 4 rows, 12 planes, per-slab XCD chunks (us per pass,
   // in brackets with 16 planes in launch order: 256^3 92 [103], 300^3 140
   // [156], 200x300x500 167 [181], 400^3 331 [336], 512^3 672 [690])
   if (dtype == J3D_F64 && pts >= (1LL << 24)) return TileCfg{4, 12, 20, 0, 2, 1};
-  // FP32 measured at 512^3: 32 rows per block, 8 planes, XCD-blocked order (4
-  // rows per thread, nontemporal stores); small grids are one latency in any
-  // shape
+  // fewer than 4096 points are one latency in any shape
   c.rows = dtype == J3D_F32 ? 8 : 4;
   c.planes = dtype == J3D_F32 ? 8 : 16;
   c.variant = 20;

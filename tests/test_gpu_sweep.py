@@ -377,7 +377,8 @@ def test_bandwidth_probe_sane():
 
 
 @pytest.mark.parametrize("shape", [(16, 16, 16), (15, 17, 16), (33, 65, 17), (64, 64, 64), (100, 250, 79), (300, 40, 146),
-                                   (128, 128, 129), (181, 143, 160), (257, 255, 256)])
+                                   (128, 128, 129), (181, 143, 160), (257, 255, 256), (257, 257, 255), (310, 300, 300),
+                                   (900, 900, 80)])
 def test_default_shapes_of_the_size_ranges(shape):
     """One, two and three sweeps with the shapes the library picks by size
     (both sides of the lines between the ranges), storing plainly (passes of
