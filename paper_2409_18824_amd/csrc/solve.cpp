@@ -252,14 +252,14 @@ int solve_fp64_fused_checks(const Field& u, const Field& f, double h, const j3d_
   Control ctl;
   J3D_TRY(read_control(s, S + 1, &ctl, st));
   long long sweeps, nh;
-  int at;
+  int at, again = 0;
   if (ctl.done) {
     sweeps = ctl.conv_at;
     nh = ctl.conv_at + 1;
     // an iterate inside a pass is formed again from the pass's input
     const bool tail = sweeps >= L * P;
     at = (int)((tail ? P + (sweeps - L * P) : sweeps / L) % 3);
-    const int again = tail ? 0 : (int)(sweeps % L);
+    again = tail ? 0 : (int)(sweeps % L);
     if (again == 1) J3D_HIP(launch_pass_one(J3D_F64, F_WRITE, cfg, one[at], nullptr, nullptr, st));
     if (again == 2) J3D_HIP(launch_sweep2_one(J3D_F64, F_WRITE, cfg2, two[at], nullptr, nullptr, st));
     if (again > 0) at = (at + 1) % 3;
@@ -270,10 +270,9 @@ int solve_fp64_fused_checks(const Field& u, const Field& f, double h, const j3d_
   }
   std::vector<double> hist;
   J3D_TRY(read_history(s, nh, &hist, st));
-  if (at != 0) {
-    J3D_TRY(to_u(at, nullptr));
-    J3D_HIP(hipStreamSynchronize(st));
-  }
+  if (at != 0) J3D_TRY(to_u(at, nullptr));
+  // (read_control waited for everything before the verdict, not for this)
+  if (again > 0 || at != 0) J3D_HIP(hipStreamSynchronize(st));
   fill_result(res, sweeps, hist[(size_t)nh - 1], hist, ctl.normf, ctl.done != 0, ctl.nonfinite != 0, o);
   return ctl.nonfinite ? fail(J3D_ENONFINITE, "residual became non-finite") : J3D_OK;
 }
@@ -470,14 +469,14 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   Control ctl;
   J3D_TRY(read_control(s, nchecks, &ctl, st));
   long long sweeps, nh;
-  int at;
+  int at, again = 0;
   if (ctl.done) {
     sweeps = ctl.conv_at * c;
     nh = ctl.conv_at + 1;
     at = which_at[(size_t)ctl.conv_at] & 1;
     // the checked iterate was formed inside a pass: form it again from the
     // pass's input, into the other array
-    const int again = which_at[(size_t)ctl.conv_at] >> 1;
+    again = which_at[(size_t)ctl.conv_at] >> 1;
     if (again == 1) J3D_HIP(launch_pass_one(J3D_F64, F_WRITE, cfg, one[at], nullptr, nullptr, st));
     if (again == 2) J3D_HIP(launch_sweep2_one(J3D_F64, F_WRITE, cfg2, two[at], nullptr, nullptr, st));
     if (again > 0) at = 1 - at;
@@ -489,10 +488,9 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   std::vector<double> hist;
   J3D_TRY(read_history(s, nh, &hist, st));
   const double resid_v = (ctl.done || S % c == 0) ? hist[(size_t)nh - 1] : ctl.value;
-  if (at == 1) {
-    J3D_TRY(to_u(nullptr));
-    J3D_HIP(hipStreamSynchronize(st));
-  }
+  if (at == 1) J3D_TRY(to_u(nullptr));
+  // (read_control waited for everything before the verdict, not for this)
+  if (again > 0 || at == 1) J3D_HIP(hipStreamSynchronize(st));
   fill_result(res, sweeps, resid_v, hist, ctl.normf, ctl.done != 0, ctl.nonfinite != 0, o);
   return ctl.nonfinite ? fail(J3D_ENONFINITE, "residual became non-finite") : J3D_OK;
 }

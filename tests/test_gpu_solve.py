@@ -321,3 +321,37 @@ def test_long_histories(S, every):
     assert np.all(np.asarray(res.history)[100:] <= np.asarray(ro.history)[100])
     assert res.resid == res.history[-1]
     assert np.array_equal(du.to_numpy(), uo)
+
+
+# the iterate that converged lies inside a pass and is formed again into u:
+# stages 1 and 2 of a pass of three checks (sweeps 7 and 8: the third pass,
+# whose input is in the last of three arrays) and of the straight schedule
+# (sweep 10 of the fourth, 5 of the second pass, whose inputs are in the other
+# array); sweep 20 is formed into the other array and copied
+@pytest.mark.parametrize("every,at", [(1, 7), (1, 8), (10, 10), (5, 5), (10, 20)])
+def test_returns_when_the_converged_iterate_is_in_place(every, at):
+    """The call blocks until u holds the reported iterate, also where the solve
+    queues work after the verdict: its stream is idle at the return, and another
+    stream reads the oracle's bits."""
+    n = (256, 256, 252) if every == 1 else (300, 300, 200)
+    say("returns when done", every, at)
+    h = 1.0 / 301
+    u0 = synth.uniform_field(*n, 15, 1, 0, 1)
+    f = synth.uniform_field(*n, 15, 2, -1, 1)
+    uo, ro = oracle.solve_plain(u0, f, h, rtol=0.0, check_every=every, max_sweeps=at)
+    before, after = ro.history[at // every - 1], ro.history[at // every]
+    assert after < before
+    rtol = float(np.sqrt(before * after) / ro.norm_f)
+    du, df = j3d.FArray.from_numpy(u0), j3d.FArray.from_numpy(f)
+    got = torch.empty_like(du.storage)
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    res = j3d.poisson_solve(du, df, h, rtol=rtol, max_sweeps=1000, check_every=every, stream=side)
+    idle = side.query()
+    with torch.cuda.stream(other):
+        got.copy_(du.storage)
+    assert idle
+    assert res.converged and res.sweeps == at and len(res.history) == at // every + 1
+    torch.cuda.synchronize()
+    du.storage.copy_(got)
+    assert np.array_equal(du.to_numpy(), uo)
