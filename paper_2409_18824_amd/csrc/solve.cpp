@@ -11,24 +11,14 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
-#include <numeric>
 #include <string>
 #include <vector>
 
 #include "runtime.h"
+#include "solve_schedule.h"
 
 namespace j3d {
 namespace {
-
-// Chunk length (in sweeps) that keeps the device busy for about 2 ms.
-long long chunk_sweeps(long long points, double bytes_per_point, long long multiple) {
-  const double t = std::max(3e-6, bytes_per_point * (double)points / 5e12);
-  long long n = (long long)std::ceil(2e-3 / t);
-  n = std::max<long long>(n, 1);
-  n = std::min<long long>(n, 1 << 16);
-  n = ((n + multiple - 1) / multiple) * multiple;
-  return n;
-}
 
 // J3D_SOLVE_SWEEPS_PER_PASS=1, 2 or 3 fixes the pass length of both modes
 // (the schedules below, with that step); unset or other values run
@@ -291,49 +281,13 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   const long long S = o.max_sweeps;
   const long long c = o.check_every;
   const long long points = (long long)u.nx() * u.ny() * u.nz();
-  // Passes of `step` sweeps: three, or two for checks after every second
-  // sweep.  Three-sweep passes run
-  // straight through the sweeps: the residual of a check is fused into the
-  // pass that forms its iterate, at that stage of the pass, whose input
-  // stays in its array until the check's verdict is known (every later
-  // kernel skips its work once a check has converged), so the checked
-  // iterate can be formed again; with checks after every sweep they carry
-  // all three residuals.  (At the end of a range a shorter pass stops before
-  // a check it would hold past its input.)  With a forced step of one or two a check group of c sweeps opens with one pass of c
-  // mod step sweeps (none when step divides c), which carries the check's
-  // residual, and continues in passes of step sweeps.
+  // Three sweeps per pass, or two for checks after every second sweep
   // (w has u's layout)
   const bool all3 = forced_step() == 0 && fit3 && three_checks_per_pass(c, points);
   long long step = forced_step() != 0 ? forced_step() : all3 ? 3 : std::min<long long>(c, 3);
   if (step == 3 && !fit3) step = 2;
-  const long long lead = c % step;
-  struct Pass {
-    int len;    // sweeps
-    int stage;  // the residual it carries is that of the iterate after this many of them; -1: none,
-                // 3: those of its input and both intermediate iterates
-  };
-  auto next_pass = [&](long long sw, long long to) -> Pass {
-    if (step != 3) {
-      const long long p = sw % c;
-      const long long len = std::min(p == 0 && lead != 0 ? lead : step, c - p);
-      return Pass{(int)std::min(len, to - sw), p == 0 ? 0 : -1};
-    }
-    if (all3) return to - sw >= 3 ? Pass{3, 3} : Pass{1, 0};
-    int len = (int)std::min<long long>(3, to - sw), stage = -1;
-    for (int o = 0; o < len; ++o) {
-      if ((sw + o) % c != 0) continue;
-      if (stage < 0)
-        stage = o;
-      else
-        len = o;  // the next check opens the next pass
-    }
-    if (stage > 0 && len < 3) return Pass{stage, -1};
-    return Pass{len, stage};
-  };
-  // the schedule repeats after `period` sweeps
-  const bool straight = step == 3 && (c >= 3 || all3);
-  const long long period = straight ? std::lcm(c, 3LL) : c;
-  const long long period_passes = straight ? period / 3 : step == 3 ? 1 : (lead != 0 ? 1 : 0) + c / step;
+  const SolveSchedule plan{c, step, all3};
+  using Pass = SolveSchedule::Pass;
 
   // the second ping-pong array, of u's layout, with u's halo
   Field w = u;
@@ -363,13 +317,13 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   // which_at[q]: 2 * (sweeps after the input of the pass that carried check
   // q) + the buffer of that input
   std::vector<unsigned char> which_at((size_t)nchecks, 0);
-  // The passes for sweeps [from, to) starting from buffer b (chunk ends are
-  // multiples of the period, so chunking never changes the schedule).
+  // The passes for sweeps [from, to) starting from buffer b (a chunk is the
+  // same passes wherever it starts).
   // Checks take their index from the device counter, so a chunk is the same
   // kernel sequence wherever it starts and can be replayed.
   auto passes = [&](long long from, long long to, int b, hipStream_t q) -> int {
     for (long long sw = from; sw < to;) {
-      const Pass ps = next_pass(sw, to);
+      const Pass ps = plan.next(sw, to);
       const unsigned fl =
           F_WRITE | (ps.stage < 0 ? 0u : ps.stage == 0 ? F_RES : ps.stage == 1 ? F_RES1 : F_RES2);
       int nt;
@@ -398,7 +352,7 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
   // the end.
   auto track = [&](long long from, long long to, int b) -> int {
     for (long long sw = from; sw < to;) {
-      const Pass ps = next_pass(sw, to);
+      const Pass ps = plan.next(sw, to);
       for (int at = 0; at < 3; ++at)
         if (ps.stage == at || ps.stage == 3) which_at[(size_t)((sw + at) / c)] = (unsigned char)(2 * at + b);
       sw += ps.len;
@@ -406,16 +360,17 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
     }
     return b;
   };
-  const long long unit = period_passes % 2 == 0 ? period : 2 * period;  // an even number of passes
-  const long long chunk = chunk_sweeps(points, 24.0 * period_passes / period, unit);
+  const SolveSchedule::Chunks chunks = plan.chunks(points);
+  const long long chunk = chunks.sweeps;
   long long sw = 0;
   int cur = 0;
   int slot = 0;
   bool seen = false;
-  // Whole chunks from one captured graph, replayed (each leaves the iterate
-  // in u again), when there are at least two of them.
-  const long long M = std::min(chunk, S / 2 / unit * unit);
-  if (M > 0) {
+  // Whole chunks from captured graphs, replayed, when there are at least two
+  // of them: one graph, or, where a chunk leaves the iterate in the other
+  // array, one for each array it starts from.
+  const long long M = std::min(chunk, S / 2 / chunks.unit * chunks.unit);
+  while (M > 0 && sw + M <= S && !seen) {
     std::string key = "fp64";
     auto add = [&key](const void* p, size_t n) { key.append(static_cast<const char*>(p), n); };
     add(one, sizeof one);
@@ -424,16 +379,17 @@ int solve_fp64(const Field& u, const Field& f, double h, const j3d_solve_opts& o
     add(&cfg, sizeof cfg);
     add(&cfg2, sizeof cfg2);
     add(&cfg3, sizeof cfg3);
-    const long long meta[6] = {c, M, nt1, nt2, nt3, step};
+    const long long meta[7] = {c, M, nt1, nt2, nt3, step, cur};
     add(meta, sizeof meta);
     const void* ptrs[3] = {s->partials, s->hist, s->ctl};
     add(ptrs, sizeof ptrs);
     add(&o.rtol, sizeof o.rtol);
     hipGraphExec_t exec = nullptr;
-    J3D_TRY(solve_graph(s, key, [&](hipStream_t q) { return passes(0, M, 0, q); }, &exec));
-    for (long long r = 0; r < S / M && !seen; ++r) {
+    J3D_TRY(solve_graph(s, key, [&](hipStream_t q) { return passes(0, M, cur, q); }, &exec));
+    const int start = cur;
+    while (sw + M <= S && !seen && cur == start) {
       J3D_HIP(hipGraphLaunch(exec, st));
-      (void)track(sw, sw + M, 0);
+      cur = track(sw, sw + M, cur);
       sw += M;
       J3D_TRY(publish_done(s, slot, st));
       if (slot > 0) J3D_TRY(poll_done(s, slot - 1, &seen));

@@ -355,3 +355,32 @@ def test_returns_when_the_converged_iterate_is_in_place(every, at):
     torch.cuda.synchronize()
     du.storage.copy_(got)
     assert np.array_equal(du.to_numpy(), uo)
+
+
+# checks far apart: chunks of whole check groups, with an odd number of passes
+# (251: 753 sweeps in 251 passes, so that replays alternate between the arrays;
+# 333: 999 in 333) and an even one whose last pass is short (1000 in 334)
+@pytest.mark.parametrize("every", [251, 333, 1000])
+@pytest.mark.parametrize("at", [0, 1, 2, 3, 7])
+def test_checks_far_apart(every, at):
+    """Early exits in the first chunks and the end of the solve, in replayed
+    chunks and in the rest after them."""
+    n = (40, 38, 36)
+    say("checks far apart", every, at)
+    h = 1.0 / 41
+    u0 = synth.uniform_field(*n, 16, 1, 0, 1)
+    f = synth.uniform_field(*n, 16, 2, -1, 1)
+    S = 3 * every * (at + 1) // 2 + 5 if at else 4 * every + 2
+    _, ro = oracle.solve_plain(u0, f, h, rtol=0.0, check_every=every, max_sweeps=S)
+    rtol = 0.0
+    if at and at < len(ro.history):
+        assert ro.history[at] < ro.history[at - 1]
+        rtol = float(np.sqrt(ro.history[at] * ro.history[at - 1]) / ro.norm_f)
+    du, df = j3d.FArray.from_numpy(u0), j3d.FArray.from_numpy(f)
+    res = j3d.poisson_solve(du, df, h, rtol=rtol, max_sweeps=S, check_every=every)
+    uo, ro = oracle.solve_plain(u0, f, h, rtol=rtol, check_every=every, max_sweeps=S)
+    assert res.converged == ro.converged == (rtol > 0.0) and res.sweeps == ro.sweeps
+    assert len(res.history) == len(ro.history)
+    assert all(rel(a, b) <= RESID_RTOL for a, b in zip(res.history, ro.history))
+    assert rel(res.resid, ro.resid) <= RESID_RTOL
+    assert np.array_equal(du.to_numpy(), uo)
