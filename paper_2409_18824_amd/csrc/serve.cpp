@@ -599,21 +599,23 @@ int queue_cycle64(j3d_server* s, const std::vector<Slot*>& slots) {
   return finish_cycle(s);
 }
 
-// Queue the copy of a finished slot's iterate to its host array: its rows
-// gathered into the slot's f (not needed any more) by a kernel, then one
-// linear copy (a strided one runs row by row, as in queue_setup).  Returns
-// whether a copy was queued; the caller synchronises before it retires the
-// slot.
-int queue_result(j3d_server* s, Slot* sl, bool* queued) {
-  const Request* q = sl->req;
-  if (q->r.u_host == nullptr) return J3D_OK;
+// A finished slot's iterate to its host array: its rows gathered into the
+// slot's f (not needed any more) by a kernel, then one linear copy (a strided
+// one runs row by row, as in queue_setup).
+int queue_gather(j3d_server* s, Slot* sl) {
+  if (sl->req->r.u_host == nullptr) return J3D_OK;
   const Field& u = sl->cur ? sl->L.w : sl->L.u;
-  double* packed = reinterpret_cast<double*>(sl->L.f.base);
-  J3D_HIP(launch_copy_box(reinterpret_cast<const double*>(u.base), u.sy, u.sz, packed, u.ex,
-                          (long long)u.ex * u.ey, u.ex, u.ey, u.ez, s->st));
-  J3D_HIP(hipMemcpyAsync(q->r.u_host, packed, (size_t)u.ex * u.ey * u.ez * sizeof(double), hipMemcpyDeviceToHost,
-                         s->st));
-  *queued = true;
+  J3D_HIP(launch_copy_box(reinterpret_cast<const double*>(u.base), u.sy, u.sz,
+                          reinterpret_cast<double*>(sl->L.f.base), u.ex, (long long)u.ex * u.ey, u.ex, u.ey, u.ez,
+                          s->st));
+  return J3D_OK;
+}
+int copy_result(j3d_server* s, Slot* sl) {
+  if (sl->req->r.u_host == nullptr) return J3D_OK;
+  const Field& u = sl->L.u;
+  J3D_HIP(hipMemcpyAsync(sl->req->r.u_host, sl->L.f.base, (size_t)u.ex * u.ey * u.ez * sizeof(double),
+                         hipMemcpyDeviceToHost, s->st));
+  J3D_HIP(hipStreamSynchronize(s->st));
   return J3D_OK;
 }
 
@@ -666,13 +668,12 @@ int worker_loop(j3d_server* s) {
     J3D_HIP(hipEventSynchronize(s->ev));
     std::vector<Slot*> keep, finished;
     const int ms = s->o.max_slots;
-    bool copies = false;
     for (Slot* sl : s->active) {
       const bool in_cycle = std::find(cyc.begin(), cyc.end(), sl) != cyc.end();
       if (!in_cycle) {
         keep.push_back(sl);
       } else if (s->h_flags[sl->id] != 0 || s->h_flags[ms + sl->id] != 0 || sl->sweeps >= sl->req->max_sweeps) {
-        J3D_TRY(queue_result(s, sl, &copies));
+        J3D_TRY(queue_gather(s, sl));
         finished.push_back(sl);
       } else {
         sl->sweeps += s->o.cycle_sweeps;
@@ -680,14 +681,15 @@ int worker_loop(j3d_server* s) {
         keep.push_back(sl);
       }
     }
-    if (copies) J3D_HIP(hipStreamSynchronize(s->st));
     // from here a slot is in `active` or retired, so that an error leaves
     // nothing for the tear-down to free twice
     s->active.swap(keep);
     s->active.insert(s->active.end(), finished.begin(), finished.end());
+    // (each result is published when its own copy is done)
     for (Slot* sl : finished) {
       const bool done = s->h_flags[sl->id] != 0, bad = s->h_flags[ms + sl->id] != 0;
       const int id = sl->id;
+      J3D_TRY(copy_result(s, sl));
       s->active.erase(std::find(s->active.begin(), s->active.end(), sl));
       J3D_TRY(retire(s, sl, done, bad, s->h_out[ms + id], s->h_out[id]));
     }

@@ -194,3 +194,24 @@ def test_host_arrays_of_ragged_requests(precision):
             uo, ro = oracle.solve_plain(np.zeros_like(f), f, h, rtol=1e-12, check_every=10, max_sweeps=30)
         assert res[k]["sweeps"] == ro.sweeps and rel(res[k]["resid"], ro.resid) <= RESID_RTOL, (k, shapes[k])
         assert np.array_equal(us[k], uo), (k, shapes[k])
+
+
+def test_results_are_published_one_by_one():
+    """Two requests that finish in the same cycle: the first is published before
+    the second's solution is copied to the host.  (A third, which does not fit
+    beside them, holds them back until both are admitted together.)  The copy
+    takes at least its bytes at 64 GB/s, the rate of the host link."""
+    n = 256
+    per = j3d.j3d_request_bytes(n, n, n)
+    say("published one by one", per)
+    with j3d.Server(hbm_budget_bytes=2 * per, max_slots=4, cycle_sweeps=10) as s:
+        first = s.submit(n, 1.0 / (n + 1), 1e-12, 200, seed=1, ny=n, nz=n + n // 2)
+        us = [np.zeros((n + 2,) * 3) for _ in range(2)]
+        both = [s.submit(n, 1.0 / (n + 1), 1e-12, 20, seed=2 + k, u_out=us[k]) for k in range(2)]
+        s.drain(timeout_s=120)
+        res = {r["ticket"]: r for r in s.poll(16)}
+    a, b = (res[t] for t in both)
+    assert min(a["t_admit"], b["t_admit"]) >= res[first]["t_done"] - 1e-3
+    assert a["sweeps"] == b["sweeps"] == 20
+    assert abs(b["t_done"] - a["t_done"]) >= us[0].nbytes / 64e9
+    assert all(np.any(u != 0.0) for u in us)
