@@ -366,8 +366,9 @@ __global__ void __launch_bounds__(256)
 __global__ void __launch_bounds__(256)
     k_publish(const unsigned* __restrict__ ctl, int words, unsigned* host_ctl, const double* __restrict__ hist, int n,
               double* host_hist) {
-  for (int q = threadIdx.x; q < words; q += 256) host_ctl[q] = ctl[q];
-  for (int q = threadIdx.x; q < n; q += 256) host_hist[q] = hist[q];
+  const int q0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
+  for (int q = q0; q < words; q += step) host_ctl[q] = ctl[q];
+  for (int q = q0; q < n; q += step) host_hist[q] = hist[q];
   __threadfence_system();
 }
 
@@ -708,7 +709,9 @@ hipError_t launch_solve_init_f32(void* a, int count, size_t apart, int ex, int e
 
 hipError_t launch_publish(const void* ctl, size_t ctl_bytes, void* host_ctl, const double* hist, int n,
                           double* host_hist, hipStream_t st) {
-  hipLaunchKernelGGL(k_publish, dim3(1), dim3(256), 0, st, static_cast<const unsigned*>(ctl), (int)(ctl_bytes / 4),
+  const int words = (int)(ctl_bytes / 4);
+  const int grid = min(64, (max(words, n) + 1023) / 1024);  // one workgroup took 152 us for 131072 of each
+  hipLaunchKernelGGL(k_publish, dim3(max(grid, 1)), dim3(256), 0, st, static_cast<const unsigned*>(ctl), words,
                      static_cast<unsigned*>(host_ctl), hist, n, host_hist);
   return hipGetLastError();
 }

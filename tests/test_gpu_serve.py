@@ -215,3 +215,23 @@ def test_results_are_published_one_by_one():
     assert a["sweeps"] == b["sweeps"] == 20
     assert abs(b["t_done"] - a["t_done"]) >= us[0].nbytes / 64e9
     assert all(np.any(u != 0.0) for u in us)
+
+
+def test_cycles_cost_what_their_requests_cost():
+    """A cycle handles the slots in use, however many there could be: the same
+    four requests take at most five times as long in a server of 65536 slots as
+    in one of 64 (what is left of the slots is 2 MB of flags and norms that go
+    to the host, some 40 us a cycle; whole tables made it 36 times)."""
+    best = {}
+    for slots in (64, 65536):
+        with j3d.Server(hbm_budget_bytes=1 << 30, max_slots=slots, cycle_sweeps=50) as s:
+            for _ in range(4):
+                t = time.perf_counter()
+                for k in range(4):
+                    s.submit(24, 1.0 / 25, 1e-300, 1000, seed=k)
+                s.drain(timeout_s=60)
+                t = time.perf_counter() - t
+                best[slots] = min(best.get(slots, t), t)
+            assert len(s.poll(64)) == 16
+    say("drain with 64 and 65536 slots", best)
+    assert best[65536] < 5 * best[64]
