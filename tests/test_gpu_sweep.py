@@ -415,3 +415,8 @@ def test_default_shapes_of_the_size_ranges(shape):
         fn(a, o, b, h)
         torch.cuda.synchronize()
         assert np.array_equal(o.to_numpy(), it[n]), n
+
+
+@pytest.mark.parametrize("shape", [(65, 65, 65), (65, 64, 63), (66, 65, 65)])
+def test_default_shapes_next_to_the_small_ones(shape):
+    test_default_shapes_of_the_size_ranges(shape)
