@@ -42,14 +42,21 @@ const std::vector<TileCfg>& tune_table() {
 //   lat + lat_row * RY + row * (rows of all workgroups on a CU)  [us]
 // (latency of a step, growing with the rows a thread walks, and the CU's
 // throughput), cap workgroups fit a CU by registers and LDS, and the last
-// round may be a partial one.  The constants are fitted to 3700 timed
-// (shape, size) pairs per pass kind over 17 sizes from 32^3 to 512x512x32;
-// the shape chosen is on average 0.3-1.7 % and at worst 9 % slower than the
-// fastest.  Against the fixed shapes before (us per pass, best stores of
-// 40-256 MB passes on both sides): FP64 two sweeps 64^3 27.5 -> 7.9, 128^3
-// 34.5 -> 17.0, 181x143x160 36 -> 25.6; three sweeps 96^3 20.5 -> 12.9,
-// 200^3 77 -> 48; FP32 two sweeps 96^3 14.5 -> 7.8, three sweeps
-// 181x143x160 31 -> 22.6.
+// round may be a partial one.  The constants were fitted to 3700 timed
+// (shape, size) pairs per pass kind over 17 sizes from 32^3 to 512x512x32,
+// the two-sweep ones on the pass that did not yet load a step ahead.  Timed
+// again on the current kernels over 16 sizes, the shape chosen is slower than
+// the fastest by, on average and at worst: FP64 two sweeps 1.6 and 6 %, three
+// 0 and 0 %; FP32 two 2.9 and 13 %, three 1.0 and 9 % (tables in
+// profiles/shape_estimates.md).  Against the fixed shapes before (us per pass,
+// best stores of 40-256 MB passes on both sides): FP64 two sweeps 64^3 27.5 ->
+// 7.2, 128^3 34.5 -> 15.2, 181x143x160 36 -> 22.4; three sweeps 96^3 20.5 ->
+// 12.6, 200^3 77 -> 47; FP32 two sweeps 96^3 14.5 -> 7.2, three sweeps
+// 181x143x160 31 -> 21.6.
+// (All of a whole card's CUs: the shapes are fitted to and timed on those.  A
+// partition runs the same shapes.)
+static constexpr int kCus = 256;
+
 TileCfg modelled_shape(int sweeps, int dtype, const Extents* e, int n) {
   const bool f32 = dtype == J3D_F32;
   struct Cost {
@@ -57,7 +64,6 @@ TileCfg modelled_shape(int sweeps, int dtype, const Extents* e, int n) {
   };
   const Cost k = sweeps == 2 ? (f32 ? Cost{0.4, 0.056, 0.006, 3} : Cost{0.5, 0.047, 0.014, 6})
                              : (f32 ? Cost{0.3, 0.0026, 0.01, 3} : Cost{0.3, 0.115, 0.042, 4});
-  constexpr int kCus = 256;
   const int width = 64 - 2 * sweeps, ring = 2 * (sweeps - 1);
   constexpr int kPlanes[] = {4, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64};
   constexpr int kNumPlanes = sizeof kPlanes / sizeof *kPlanes;
@@ -169,7 +175,7 @@ TileCfg default_cfg3(int dtype, int nx, int ny, int nz) {
     c = TileCfg{4, 24, 20, 0, 0, 1};
     int tx, ty, tz;
     tile3_counts(nx, ny, nz, c, &tx, &ty, &tz);
-    if ((long long)tx * ty * tz <= 5 * 256) return c;
+    if ((long long)tx * ty * tz <= 5 * kCus) return c;
   }
   // FP64 above 400^3: 16 wavefronts of 2 rows (32-row blocks, one workgroup
   // per CU), 144 planes in launch order (512^3 712 us per pass against 731
@@ -184,23 +190,23 @@ TileCfg default_cfg3(int dtype, int nx, int ny, int nz) {
     c = TileCfg{16, 144, 6, 0, 1, 1};
     int tx, ty, tz;
     tile3_counts(nx, ny, nz, c, &tx, &ty, &tz);
-    const long long tiles = (long long)tx * ty * tz, last = tiles % 256;
-    if (tiles < 4 * 256 && last > 0 && last < 128) {
+    const long long tiles = (long long)tx * ty * tz, last = tiles % kCus;
+    if (tiles < 4 * kCus && last > 0 && last < kCus / 2) {
       const TileCfg s{16, 32, 6, 0, 2, 1};
       tile3_counts(nx, ny, nz, s, &tx, &ty, &tz);
       if ((long long)tx * ty * tz <= 65536) c = s;
     }
     return c;
   }
-  // Otherwise, up to 2^24 points (FP32 300^3), 4 wavefronts of 4 rows per
-  // thread, 16 planes in per-slab XCD chunks; beyond, 8 wavefronts of 2 rows
-  // per thread (about 95 registers per thread against 160 with 4 rows, so
-  // twice the wavefronts per CU), 32 planes (FP64 300x320x280 165 us against
-  // 177 with 4 x 4 rows, 280x300x260 121; at 256^3, whose default is older, 109
-  // against 115); FP32 above 400^3 48 planes
-  // (512^3 419 us against 439 with 4 wavefronts of 4 rows and 24 planes).
-  // Below 200^3 points only grids too flat for the model come here: 4
-  // wavefronts of 2 rows, XCD-blocked.
+  // Otherwise 8 wavefronts of 2 rows per thread (about 95 registers per thread
+  // against 160 with 4 rows, so twice the wavefronts per CU), 32 planes in
+  // per-slab XCD chunks (FP64 300x320x280 165 us against 177 with 4 x 4 rows,
+  // 280x300x260 121); FP32 above 400^3 48 planes (512^3 419 us against 439
+  // with 4 wavefronts of 4 rows and 24 planes), FP32 up to 300^3 4 wavefronts
+  // of 4 rows, 16 planes.  FP64 256^3 itself keeps those too, the default that
+  // the tests hold it to (111 us, with a residual 125, against 109 and 120).
+  // Grids below 2^24 points come here only when too flat for the model: 4
+  // wavefronts, up to 200^3 points of 2 rows and XCD-blocked.
   const bool small = pts <= 200LL * 200 * 200;
   const bool large = pts > (dtype == J3D_F32 ? 300LL * 300 * 300 : 1LL << 24);
   c.rows = large ? 8 : 4;

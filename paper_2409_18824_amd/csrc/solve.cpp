@@ -22,10 +22,12 @@ namespace {
 
 // J3D_SOLVE_SWEEPS_PER_PASS=1, 2 or 3 fixes the pass length of both modes
 // (the schedules below, with that step); unset or other values run
-// three-sweep passes where the cadence of the checks lets them: they take
+// three-sweep passes where the cadence of the checks lets them.  A pass takes
 // less time per sweep at every size (us per sweep in passes of three against
-// two: FP64 64^3 3.4 / 3.9, 128^3 6.7 / 8.5, 200^3 16 / 20, 512^3 237 / 345;
-// FP32 64^3 2.9 / 3.3, 128^3 5.4 / 6.2, 256^3 18 / 21, 512^3 142 / 200).
+// two: FP64 64^3 3.4 / 3.6, 128^3 6.7 / 7.7, 200^3 15.7 / 19.0, 512^3 236 /
+// 335; FP32 64^3 2.9 / 3.0, 128^3 5.2 / 5.5, 256^3 17 / 20, 512^3 140 / 188);
+// whole solves of 40^3 with a check every 50 sweeps would take 5 % less in
+// passes of two, of 100^3 1 %, of 64^3 the same.
 int forced_step() {
   const char* e = std::getenv("J3D_SOLVE_SWEEPS_PER_PASS");
   const int v = e != nullptr ? std::atoi(e) : 0;
