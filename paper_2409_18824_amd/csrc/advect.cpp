@@ -15,7 +15,11 @@ namespace {
 
 // A workgroup shape and what a step of its march costs (us) with j workgroups
 // on a CU: h + g * j, at most `per_cu` of them.  Fitted to timed passes over
-// nine grids from 64^3 to 1024 x 512 x 512.
+// nine grids from 64^3 to 1024 x 512 x 512; the shapes they choose are on
+// average 3 % (tracer 4 %) and at worst 13 % (8 %) slower than the fastest of
+// 60 (profiles/shape_estimates.md).  CUs: those of a whole card, which they
+// were timed on.
+constexpr int kCus = 256;
 struct MarchShape {
   int ry, cols, rows;  // rows per thread; columns and rows a workgroup outputs
   int per_cu;
@@ -37,7 +41,7 @@ AdvectCfg march_shape(const MarchShape (&shapes)[N], const AdvArgs& a) {
         ((a.nx + s.cols - 1LL) / s.cols) * ((a.ny + s.rows - 1LL) / s.rows);
     for (int planes = 4; planes <= 128; ++planes) {
       const int chunks = (a.nz + planes - 1) / planes;
-      const long long per_cu = (tiles * chunks + 255) / 256;
+      const long long per_cu = (tiles * chunks + kCus - 1) / kCus;
       const long long full = per_cu / s.per_cu, rest = per_cu % s.per_cu;
       const double t = (std::min(planes, a.nz) + s.extra) *
                        (full * (s.h + s.g * s.per_cu) + (rest ? s.h + s.g * rest : 0.0));
@@ -90,9 +94,9 @@ bool plane_below_2gib(const Field& a) {
   return ((long long)(a.ey - 1) * a.sy + a.ex) * (long long)a.esize < (1LL << 31);
 }
 
-// Two-step tracer pass (planes of 2^31 bytes and more): 6 rows per thread, 64 planes, nontemporal stores
-// (fastest at 1024 x 512 x 512).  J3D_TRACER2_TILE="ry,planes,nt" overrides
-// it.
+// Two-step tracer pass (planes of 2^31 bytes and more): 6 rows per thread, 64
+// planes, nontemporal stores (fastest at 1024 x 512 x 512).
+// J3D_TRACER2_TILE="ry,planes,nt" overrides it.
 AdvectCfg tracer2_cfg() {
   AdvectCfg c{6, 64, 1};
   if (const char* e = std::getenv("J3D_TRACER2_TILE")) {

@@ -28,6 +28,8 @@ namespace {
 
 using sweep_detail::from_left;
 using sweep_detail::from_right;
+using sweep_detail::shift_in_left;
+using sweep_detail::shift_in_right;
 using sweep_detail::WAVE;
 
 constexpr int kWavesPerBlock = 4;
@@ -78,25 +80,6 @@ __global__ void __launch_bounds__(WAVE * kWavesPerBlock)
     const int y = y0 + r;
     if (lane_out && y >= 1 && y <= ny) out[x + so * y] = v[r];
   }
-}
-
-// The value of lane l-1 (shift_right_lane) or l+1 (shift_left_lane) of the
-// wavefront; the lane at the end gets 0 (it only feeds cells that are not
-// stored).  One DPP move per 32-bit half.
-typedef int i2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ double shift_right_lane(double v) {
-  const i2 a = __builtin_bit_cast(i2, v);
-  i2 r;
-  r.x = __builtin_amdgcn_mov_dpp(a.x, 0x138, 0xF, 0xF, true);
-  r.y = __builtin_amdgcn_mov_dpp(a.y, 0x138, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, r);
-}
-__device__ __forceinline__ double shift_left_lane(double v) {
-  const i2 a = __builtin_bit_cast(i2, v);
-  i2 r;
-  r.x = __builtin_amdgcn_mov_dpp(a.x, 0x130, 0xF, 0xF, true);
-  r.y = __builtin_amdgcn_mov_dpp(a.y, 0x130, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, r);
 }
 
 // T sweeps per launch by a workgroup of BY wavefronts stacked in y, each
@@ -204,7 +187,7 @@ __device__ __forceinline__ void jacobi2d_pair_sweeps(double (&v)[R][2], const bo
 #pragma unroll
     for (int q = 0; q < R; ++q) {
       const int r = q + 1 < R ? q + 1 : 0;  // 1 .. R-1, then 0
-      const double left = shift_right_lane(a[r][1]), right = shift_left_lane(a[r][0]);
+      const double left = shift_in_left(a[r][1]), right = shift_in_right(a[r][0]);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         double t = c == 0 ? left + a[r][1] : a[r][0] + right;

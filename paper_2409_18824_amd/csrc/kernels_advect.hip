@@ -42,6 +42,8 @@ using sweep_detail::from_left;
 using sweep_detail::from_right;
 using sweep_detail::lane_value;
 using sweep_detail::put;
+using sweep_detail::shift_in_left;
+using sweep_detail::shift_in_right;
 using sweep_detail::WAVE;
 using sweep_detail::xcd_remap;
 
@@ -83,34 +85,16 @@ __device__ __forceinline__ TileMap tile_of(const AdvArgs& a, int ry) {
   return m;
 }
 
-// The value of lane l-1 / l+1; zero in lane 0 / lane 63, whose neighbour the
-// callers take from elsewhere or do not use (nothing to keep there, so the
-// shift needs no copy of its operand first).
-__device__ __forceinline__ double left_lane(double v) {
-  const sweep_detail::dpp_i2 a = __builtin_bit_cast(sweep_detail::dpp_i2, v);
-  sweep_detail::dpp_i2 r;
-  r.x = __builtin_amdgcn_mov_dpp(a.x, 0x138, 0xF, 0xF, true);
-  r.y = __builtin_amdgcn_mov_dpp(a.y, 0x138, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, r);
-}
-__device__ __forceinline__ double right_lane(double v) {
-  const sweep_detail::dpp_i2 a = __builtin_bit_cast(sweep_detail::dpp_i2, v);
-  sweep_detail::dpp_i2 r;
-  r.x = __builtin_amdgcn_mov_dpp(a.x, 0x130, 0xF, 0xF, true);
-  r.y = __builtin_amdgcn_mov_dpp(a.y, 0x130, 0xF, 0xF, true);
-  return __builtin_bit_cast(double, r);
-}
-
 // Left / right x-neighbour of value v of row r, whose halo columns are in
 // the gathered vector g (lane r: left, lane 32+r: right).
 __device__ __forceinline__ double nb_left(double v, double g, int r, int lane) {
   const double h = lane_value(g, r);
-  const double s = left_lane(v);
+  const double s = shift_in_left(v);
   return lane == 0 ? h : s;
 }
 __device__ __forceinline__ double nb_right(double v, double g, int r, int lane) {
   const double h = lane_value(g, 32 + r);
-  const double s = right_lane(v);
+  const double s = shift_in_right(v);
   return lane == WAVE - 1 ? h : s;
 }
 
@@ -664,8 +648,8 @@ __global__ void __launch_bounds__(WAVE * WV, 8 / WV) k_tracer3_advect(AdvArgs a)
 #pragma unroll
     for (int r = 0; r < RY; ++r) {
       const double tc = t[r];
-      const double fe = upwind_plain(f.u[r], tc, right_lane(tc));
-      const double fw = left_lane(fe);
+      const double fe = upwind_plain(f.u[r], tc, shift_in_right(tc));
+      const double fw = shift_in_left(fe);
       const double fn = upwind_plain(f.v[r + 1], tc, r == RY - 1 ? tn : t[r + 1]);
       const double ft = upwind_plain(f.w[r], tc, up[r]);
       const double div = ((fe - fw) + (fn - fs)) + (ft - bot[r]);
