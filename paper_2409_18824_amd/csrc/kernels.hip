@@ -362,13 +362,15 @@ __global__ void __launch_bounds__(256)
 
 // The control block and the first n entries of the history into pinned host
 // memory, which a host that waits for the stream then reads (a copy command
-// takes the stream 15 us for each).
+// takes the stream 15 us for each).  GRID workgroups: one, or 64 for a server
+// of many slots (131072 words and as many norms take one workgroup 152 us).
+template <int GRID>
 __global__ void __launch_bounds__(256)
     k_publish(const unsigned* __restrict__ ctl, int words, unsigned* host_ctl, const double* __restrict__ hist, int n,
               double* host_hist) {
-  const int q0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
-  for (int q = q0; q < words; q += step) host_ctl[q] = ctl[q];
-  for (int q = q0; q < n; q += step) host_hist[q] = hist[q];
+  const int q0 = (GRID > 1 ? (int)blockIdx.x * 256 : 0) + (int)threadIdx.x;
+  for (int q = q0; q < words; q += GRID * 256) host_ctl[q] = ctl[q];
+  for (int q = q0; q < n; q += GRID * 256) host_hist[q] = hist[q];
   __threadfence_system();
 }
 
@@ -710,9 +712,9 @@ hipError_t launch_solve_init_f32(void* a, int count, size_t apart, int ex, int e
 hipError_t launch_publish(const void* ctl, size_t ctl_bytes, void* host_ctl, const double* hist, int n,
                           double* host_hist, hipStream_t st) {
   const int words = (int)(ctl_bytes / 4);
-  const int grid = min(64, (max(words, n) + 1023) / 1024);  // one workgroup took 152 us for 131072 of each
-  hipLaunchKernelGGL(k_publish, dim3(max(grid, 1)), dim3(256), 0, st, static_cast<const unsigned*>(ctl), words,
-                     static_cast<unsigned*>(host_ctl), hist, n, host_hist);
+  const bool many = max(words, n) > 4096;  // a solve sends up to 4096 entries
+  hipLaunchKernelGGL(many ? k_publish<64> : k_publish<1>, dim3(many ? 64 : 1), dim3(256), 0, st,
+                     static_cast<const unsigned*>(ctl), words, static_cast<unsigned*>(host_ctl), hist, n, host_hist);
   return hipGetLastError();
 }
 
